@@ -16,8 +16,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "librgcsr.so")
 BUILD_DIR = os.path.join(HERE, "_build")
-SOURCES = ["host_layout.cpp", "ordering.cpp", "tile_layout.cpp", "panel_layout.cpp", "abi_host.cpp", "abi.cpp", "autotune.cpp", "kernels.hip",
-           "convert.hip", "tiles.hip"]
+SOURCES = ["host_layout.cpp", "ordering.cpp", "tile_layout.cpp", "panel_layout.cpp", "compact_layout.cpp", "abi_host.cpp",
+           "abi.cpp", "autotune.cpp", "kernels.hip", "compact.hip", "convert.hip", "tiles.hip"]
 ARCH = os.environ.get("RGCSR_OFFLOAD_ARCH", "gfx950")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

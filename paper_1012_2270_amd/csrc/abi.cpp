@@ -12,6 +12,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "compact.h"
 #include "convert.h"
 #include "internal.h"
 #include "kernels.h"
@@ -125,6 +126,12 @@ struct rgcsr_matrix_s {
     void *tile_mem = nullptr;
     size_t tile_bytes = 0;
     std::shared_ptr<HostTiles> pending_tiles;  // host arrays until they are uploaded
+    // compact columns of the grouped rows (compact.h)
+    int32_t compact = kCompactNone, compact_rows = 1, compact_width = 0, n_pat = 0, pat_stride = 0;
+    uint8_t *pat_id = nullptr;
+    int32_t *pat_tab = nullptr, *win = nullptr;
+    uint16_t *col16 = nullptr;
+    std::shared_ptr<HostCompact> pending_compact;  // host arrays until they are uploaded
     // column panels (panel_layout.cpp): PN is a handle of its own over the
     // stacked pieces, used by launches whose x slice per panel fits an L2;
     // the arrays below belong to PN and live in its block
@@ -306,6 +313,31 @@ void upload_tiles(rgcsr_matrix_s *h, const HostTiles &T, const std::vector<int32
     HIPCHK(hipStreamSynchronize(st));
 }
 
+// The compact columns serve the automatic schedule only: explicit kernel
+// schedules name how the layout's own columns are walked.  (Long rows exclude
+// them too.)
+bool compact_wanted(const LayoutParams &p, int32_t rows_per_lane, int32_t pad_loads, int32_t load_policy) {
+    return p.T == 1 && p.G % 64 == 0 && rows_per_lane == 0 && pad_loads < 0 && load_policy == 0;
+}
+
+// Compact arrays of the handle, listed in arena a.  C: HostCompact, or the
+// DevCompact of a conversion on the device.
+template <class C> void add_compact_arrays(rgcsr_matrix_s *h, const C &c, Arena &a) {
+    h->compact = c.mode;
+    h->compact_rows = c.rows;
+    h->compact_width = c.width;
+    if (c.mode == kCompactPattern) {
+        h->n_pat = c.n_pat;
+        h->pat_stride = c.stride;
+        a.add(&h->pat_id, (size_t)h->ns);
+        a.add(&h->pat_tab, (size_t)c.n_pat * c.stride);
+    } else if (c.mode == kCompactWindow) {
+        const int64_t per = (int64_t)kBlockWaves * c.rows;
+        a.add(&h->col16, (size_t)h->slots);
+        a.add(&h->win, (size_t)(2 * ((h->ng + per - 1) / per)));
+    }
+}
+
 std::vector<int32_t> panel_unit_map(const rgcsr_matrix_s *h, const HostLayout &L, const PanelBuilt &pb,
                                     bool use_rows);
 
@@ -370,6 +402,13 @@ rgcsr_matrix_s *prepare_handle(const HostLayout &L, bool with_row_ptr, const Hos
         build_tiles(L, tile_min_len, *tiles);
         add_tile_arrays(h, *tiles, a);
         if (tiles->active()) h->pending_tiles = tiles;
+        // (a panel copy serves several right-hand sides over random columns)
+        if (!pb && compact_wanted(h->prm, rows_per_lane, pad_loads, load_policy)) {
+            auto C = std::make_shared<HostCompact>();
+            build_compact(L, *C);
+            add_compact_arrays(h, *C, a);
+            if (C->mode != kCompactNone) h->pending_compact = C;
+        }
         if (pb) {
             // panel copy: workgroup tables for both schedules, the pieces of
             // each output row, and the per-piece sums
@@ -429,11 +468,18 @@ void place_and_upload(rgcsr_matrix_s *h, Arena &a, const HostLayout &L, const st
         if (map->long_nnz) HIPCHK(hipMemcpyAsync(h->t_map_long, map->long_val.data(), (size_t)map->long_nnz * 4, hipMemcpyHostToDevice, st));
     }
     if (h->pending_tiles) upload_tiles(h, *h->pending_tiles, L.long_row, st);
+    if (h->pending_compact) {
+        upload(h->pat_id, h->pending_compact->pat_id, st);
+        upload(h->pat_tab, h->pending_compact->pat_tab, st);
+        upload(h->win, h->pending_compact->win, st);
+        upload(h->col16, h->pending_compact->col16, st);
+    }
     int32_t *const map_dst[5] = {h->unit_map_rows, h->unit_map_one, h->pan_crow, h->pan_cptr, h->pan_vidx};
     for (int i = 0; i < 5; i++)
         if (h->pending_maps[i]) upload(map_dst[i], *h->pending_maps[i], st);
     HIPCHK(hipStreamSynchronize(st));
     h->pending_tiles.reset();
+    h->pending_compact.reset();
     for (auto &m : h->pending_maps) m.reset();
 }
 
@@ -513,10 +559,14 @@ rgcsr_matrix_s *make_device_on_device(DevPlan &P, const LayoutParams &p, int vdt
         a.add(&h->long_col, (size_t)L.long_nnz);
         a.add((uint8_t **)&h->partial, (size_t)L.work.n_partials * 32 * sizeof(double));
         if (keep_map) a.add(&h->row_ptr, (size_t)P.n_rows + 1);
+        const DevCompact C = P.nl == 0 && P.ns > 0 && compact_wanted(p, rows_per_lane, pad_loads, load_policy)
+                                 ? device_compact(P, p, h->esz, rp, col, st) : DevCompact();
+        add_compact_arrays(h, C, a);
         h->mem = a.commit();
         h->bytes = a.total;
         device_fill(P, p, rp, col, vals, vals_dt, vdt, h->gp, h->short_len, h->perm ? h->short_row : nullptr,
                     h->slot_val, h->slot_col, h->long_row, h->long_ptr, h->long_val, h->long_col, st);
+        device_compact_fill(P, C, h->gp, h->slot_col, h->pat_id, h->pat_tab, h->win, h->col16, st);
         upload(h->short_items, h->items, st);
         upload(h->wave_work, L.work.wave, st);
         upload(h->block_work, L.work.block, st);
@@ -648,6 +698,9 @@ SpmvParams params_of(const rgcsr_matrix_s *h, bool use_rows, bool tiled = false)
     P.wave_work = h->wave_work; P.block_work = h->block_work;
     P.long_row = h->long_row; P.long_ptr = h->long_ptr; P.long_val = h->long_val;
     P.long_col = h->long_col; P.partial = h->partial;
+    P.compact = h->compact;
+    P.pat_ints = h->n_pat * h->pat_stride; P.pat_stride = h->pat_stride; P.last_col = (int32_t)(h->n_cols - 1);
+    P.pat_id = h->pat_id; P.pat_tab = h->pat_tab; P.col16 = h->col16; P.win = h->win;
     P.tile_dst = h->n_tent ? h->tile_dst : nullptr;
     P.tile_vals = h->n_tent ? h->tile_val : nullptr;
     int64_t n_block = h->n_block, n_wave_long = h->n_wave_long, n_comb = 0;
@@ -768,7 +821,12 @@ void spmv_launch(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx, voi
         e = launch_tile_spmv(TP, vd, (int)h->n_tunits, st);
         if (e != hipSuccess) fail(RGCSR_EHIP, std::string("tile launch: ") + hipGetErrorString(e));
     }
-    e = launch_spmv(P, vd, f64, h->prm.T, K, R, K == 1 ? h->lp : 0, (int)nwg, st);
+    if (h->compact != kCompactNone && K == 1) {
+        P.n_wave_items = (int32_t)((h->ng * h->wpg + h->compact_rows - 1) / h->compact_rows);
+        e = launch_spmv_compact(P, vd, f64, h->compact_rows, h->compact_width, st);
+    } else {
+        e = launch_spmv(P, vd, f64, h->prm.T, K, R, K == 1 ? h->lp : 0, (int)nwg, st);
+    }
     if (e != hipSuccess) fail(RGCSR_EHIP, std::string("spmv launch: ") + hipGetErrorString(e));
     const int64_t n_comb = tiled ? h->n_rest_combine : h->n_combine;
     if (n_comb) {
@@ -835,7 +893,8 @@ rgcsr_status rgcsr_from_csr(int64_t n_rows, int64_t n_cols, int64_t nnz, const i
         // conversion on the device; device inputs are always validated
         DevPlan P;
         P.scratch.st = st;
-        device_plan(P, p, n_rows, n_cols, nnz, row_ptr, col_idx, true, st);
+        device_plan(P, p, n_rows, n_cols, nnz, row_ptr, col_idx, true,
+                    compact_wanted(p, o.rows_per_lane, o.pad_loads, o.load_policy), st);
         *out = make_device_on_device(P, p, o.value_dtype, row_ptr, col_idx, vals, vals_dtype, o.keep_csr_map != 0, st,
                                      o.rows_per_lane, o.pad_loads, o.load_policy, o.tile_min_len);
         return RGCSR_OK;
@@ -1301,7 +1360,8 @@ rgcsr_matrix_s *clone_handle(const rgcsr_matrix_s *A, hipStream_t st) {
                &rgcsr_matrix_s::row_ptr, &rgcsr_matrix_s::t_map_slot,
                &rgcsr_matrix_s::t_map_long, &rgcsr_matrix_s::unit_map_rows, &rgcsr_matrix_s::unit_map_one,
                &rgcsr_matrix_s::pan_crow, &rgcsr_matrix_s::pan_cptr, &rgcsr_matrix_s::pan_vidx,
-               &rgcsr_matrix_s::pan_y);
+               &rgcsr_matrix_s::pan_y, &rgcsr_matrix_s::pat_id, &rgcsr_matrix_s::pat_tab, &rgcsr_matrix_s::col16,
+               &rgcsr_matrix_s::win);
         // tile arrays: in the same block, or in a block of their own
         auto tile_rebase = [&](void *rgcsr_matrix_s::*block) {
             rebase(h, A, block, &rgcsr_matrix_s::tile_units, &rgcsr_matrix_s::tile_ptr, &rgcsr_matrix_s::tile_dst,

@@ -12,11 +12,16 @@
 
 namespace rg {
 
-// Device scratch of one conversion; freed by the destructor.
+// Device scratch of one conversion, carved from a few blocks (one hipMalloc
+// and hipFree for most of it: a small matrix would otherwise spend more time
+// on some twenty allocations than on its kernels); freed by the destructor.
 struct DevScratch {
     std::vector<void *> bufs;
+    char *at = nullptr;        // free part of the last block
+    size_t left = 0;
     hipStream_t st = nullptr;  // work on it finishes before the buffers are freed
-    void *get(size_t bytes);
+    void reserve(size_t bytes);  // starts a block of at least this size
+    void *get(size_t bytes);     // 256-byte aligned
     ~DevScratch();
 };
 
@@ -36,13 +41,18 @@ struct DevPlan {
     const int32_t *lens_s = nullptr; // [ns] their lengths
     const int64_t *gp = nullptr;     // [ng + 1]
     const int64_t *long_ptr = nullptr;  // [nl + 1]
+    // row patterns (compact.h), searched when the caller may use them
+    int32_t n_pat = 0, pat_stride = 0;  // n_pat = 0: none
+    const uint8_t *pat_id = nullptr;    // [n_rows] in CSR row order
+    const int32_t *pat_tab = nullptr;   // [n_pat * pat_stride]
     DevScratch scratch;
 };
 
 // Validates the device CSR when asked (RGCSR_ECSR on malformed input) and
-// computes the plan.  Synchronises the stream.
+// computes the plan, with the row patterns when asked and there are no long
+// rows.  Synchronises the stream.
 void device_plan(DevPlan &P, const LayoutParams &p, int64_t n_rows, int64_t n_cols, int64_t nnz,
-                 const int64_t *rp, const int32_t *col, bool validate, hipStream_t st);
+                 const int64_t *rp, const int32_t *col, bool validate, bool patterns, hipStream_t st);
 
 // Writes the layout arrays (device pointers of the handle; short_row only
 // when P.perm) from the device CSR, values converted from vals_dt to vdt.
@@ -50,5 +60,20 @@ void device_fill(const DevPlan &P, const LayoutParams &p, const int64_t *rp, con
                  int vals_dt, int vdt, int64_t *gp, int32_t *short_len, int32_t *short_row, void *slot_val,
                  int32_t *slot_col, int32_t *long_row, int64_t *long_ptr, void *long_val, int32_t *long_col,
                  hipStream_t st);
+
+// Compact columns of the planned layout (compact.h; esz: bytes of a stored
+// value): the plan's patterns, else x windows searched in the device CSR
+// arrays (synchronises the stream).  The arrays stay in the plan's scratch
+// until device_compact_fill writes the handle's.
+struct DevCompact {
+    int mode = 0;  // kCompact*
+    int32_t rows = 1, width = 0, n_pat = 0, stride = 0;  // as HostCompact
+    int64_t units = 0;
+    const int32_t *win = nullptr;  // [2 * units]
+};
+DevCompact device_compact(DevPlan &P, const LayoutParams &p, int esz, const int64_t *rp, const int32_t *col,
+                          hipStream_t st);
+void device_compact_fill(const DevPlan &P, const DevCompact &C, const int64_t *gp, const int32_t *slot_col,
+                         uint8_t *pat_id, int32_t *pat_tab, int32_t *win, uint16_t *col16, hipStream_t st);
 
 }  // namespace rg

@@ -12,14 +12,26 @@
 #include <rocprim/device/device_scan.hpp>
 #include <rocprim/device/device_select.hpp>
 
+#include "compact.h"
 #include "convert.h"
 
 namespace rg {
 
-void *DevScratch::get(size_t bytes) {
+void DevScratch::reserve(size_t bytes) {
     void *p = nullptr;
+    bufs.reserve(bufs.size() + 1);
     if (hipMalloc(&p, bytes ? bytes : 1) != hipSuccess) fail(RGCSR_ENOMEM, "device scratch allocation failed");
     bufs.push_back(p);
+    at = (char *)p;
+    left = bytes;
+}
+
+void *DevScratch::get(size_t bytes) {
+    bytes = (bytes + 255) / 256 * 256;
+    if (bytes > left) reserve(bytes > (size_t(1) << 20) ? bytes : size_t(1) << 20);
+    void *p = at;
+    at += bytes;
+    left -= bytes;
     return p;
 }
 
@@ -215,7 +227,7 @@ template <class F> void with_temp(DevScratch &S, F f) {
 }  // namespace
 
 void device_plan(DevPlan &P, const LayoutParams &p, int64_t n_rows, int64_t n_cols, int64_t nnz,
-                 const int64_t *rp, const int32_t *col, bool validate, hipStream_t st) {
+                 const int64_t *rp, const int32_t *col, bool validate, bool patterns, hipStream_t st) {
     if (n_rows < 0 || n_cols < 0 || nnz < 0) fail(RGCSR_EINVAL, "negative size");
     if (n_rows > INT32_MAX || n_cols > INT32_MAX)
         fail(RGCSR_EOVERFLOW, "n_rows and n_cols must fit int32 column/row indices");
@@ -225,8 +237,16 @@ void device_plan(DevPlan &P, const LayoutParams &p, int64_t n_rows, int64_t n_co
     P.nnz = nnz;
     DevScratch &S = P.scratch;
     const int64_t n = n_rows;
-    int32_t *flags = (int32_t *)S.get(8);
-    CHK(hipMemsetAsync(flags, 0, 8, st));
+    // about what the steps below take: row arrays and the groups', the sort
+    // keys, the split lists (the long rows' own arrays come on top)
+    const bool sorted = p.sigma > 1, split = p.tau >= 0;
+    S.reserve((size_t)n * (18 + (sorted ? 40 : 0) + (split ? 14 : 0)) + (size_t(1) << 17));
+    // one block of what starts at zero: error and layout flags, the pattern
+    // search's state and hash table
+    int32_t *flags = (int32_t *)S.get(64 + kPatHash * sizeof(uint64_t));
+    int32_t *pat_state = flags + 4;
+    uint64_t *pat_key = (uint64_t *)(flags + 16);
+    CHK(hipMemsetAsync(flags, 0, 64 + (patterns ? kPatHash * sizeof(uint64_t) : 0), st));
     if (validate) {
         hipLaunchKernelGGL(validate_k, dim3(nblocks(n)), dim3(256), 0, st, rp, col, n, n_cols, nnz, flags);
         CHK(hipGetLastError());
@@ -252,12 +272,8 @@ void device_plan(DevPlan &P, const LayoutParams &p, int64_t n_rows, int64_t n_co
     // window order: stable radix sort of (window, longest first)
     int32_t *len = (int32_t *)S.get(n * 4);
     int32_t *ord = (int32_t *)S.get(n * 4);
-    uint64_t *key = nullptr;
-    if (p.sigma > 1 && p.sigma < n) {
-        key = (uint64_t *)S.get(n * 8);
-    } else if (p.sigma >= n) {
-        key = (uint64_t *)S.get(n * 8);  // one window: the key is the length alone
-    }
+    // (one window: the key is the length alone)
+    uint64_t *key = sorted || p.sigma >= n ? (uint64_t *)S.get(n * 8) : nullptr;
     int32_t *row_tmp = key ? (int32_t *)S.get(n * 4) : ord;
     hipLaunchKernelGGL(keys_k, dim3(nblocks(n)), dim3(256), 0, st, rp, n, std::max<int64_t>(1, p.sigma), len, key,
                        row_tmp);
@@ -273,19 +289,24 @@ void device_plan(DevPlan &P, const LayoutParams &p, int64_t n_rows, int64_t n_co
         });
     }
     // long-row split, both lists in window order
-    uint8_t *fs = (uint8_t *)S.get(n), *fl = (uint8_t *)S.get(n);
-    hipLaunchKernelGGL(split_k, dim3(nblocks(n)), dim3(256), 0, st, ord, len, n, p.tau, fs, fl);
-    CHK(hipGetLastError());
-    int32_t *sv = (int32_t *)S.get(n * 4);
-    int32_t *lv0 = (int32_t *)S.get(n * 4);
-    size_t *counts = (size_t *)S.get(2 * sizeof(size_t));
-    with_temp(S, [&](void *t, size_t &b) { return rocprim::select(t, b, ord, fs, sv, counts, (size_t)n, st); });
-    with_temp(S, [&](void *t, size_t &b) { return rocprim::select(t, b, ord, fl, lv0, counts + 1, (size_t)n, st); });
-    size_t hc[2];
-    CHK(hipMemcpyAsync(hc, counts, sizeof(hc), hipMemcpyDeviceToHost, st));
-    CHK(hipStreamSynchronize(st));
-    P.ns = (int64_t)hc[0];
-    P.nl = (int64_t)hc[1];
+    int32_t *sv = ord, *lv0 = nullptr;
+    P.ns = n;
+    P.nl = 0;
+    if (split) {
+        uint8_t *fs = (uint8_t *)S.get(n), *fl = (uint8_t *)S.get(n);
+        hipLaunchKernelGGL(split_k, dim3(nblocks(n)), dim3(256), 0, st, ord, len, n, p.tau, fs, fl);
+        CHK(hipGetLastError());
+        sv = (int32_t *)S.get(n * 4);
+        lv0 = (int32_t *)S.get(n * 4);
+        size_t *counts = (size_t *)S.get(2 * sizeof(size_t));
+        with_temp(S, [&](void *t, size_t &b) { return rocprim::select(t, b, ord, fs, sv, counts, (size_t)n, st); });
+        with_temp(S, [&](void *t, size_t &b) { return rocprim::select(t, b, ord, fl, lv0, counts + 1, (size_t)n, st); });
+        size_t hc[2];
+        CHK(hipMemcpyAsync(hc, counts, sizeof(hc), hipMemcpyDeviceToHost, st));
+        CHK(hipStreamSynchronize(st));
+        P.ns = (int64_t)hc[0];
+        P.nl = (int64_t)hc[1];
+    }
     const int64_t ns = P.ns, nl = P.nl;
     // grouped rows: lengths, order and emptiness flags, group widths, offsets
     int32_t *lens_s = (int32_t *)S.get(std::max<int64_t>(1, ns) * 4);
@@ -325,13 +346,23 @@ void device_plan(DevPlan &P, const LayoutParams &p, int64_t n_rows, int64_t n_co
             return rocprim::inclusive_scan(t, b, ll, lp + 1, (size_t)nl, rocprim::plus<int64_t>(), st);
         });
     }
+    patterns = patterns && nl == 0;
+    if (patterns) {
+        uint8_t *id = (uint8_t *)S.get(n);
+        int32_t *tab = (int32_t *)S.get(kPatTab * sizeof(int32_t));
+        CHK(launch_find_patterns(rp, col, n, pat_key, (int32_t *)S.get(2 * kPatHash * sizeof(int32_t)), pat_state,
+                                 (uint16_t *)S.get(n * 2), id, tab, st));
+        P.pat_id = id;
+        P.pat_tab = tab;
+    }
     P.gp_host.resize(P.ng + 1);
-    P.long_ptr_host.resize(nl + 1);
-    int32_t hf = 0;
+    P.long_ptr_host.assign(nl + 1, 0);
+    int32_t small[8];
     CHK(hipMemcpyAsync(P.gp_host.data(), gp, (P.ng + 1) * 8, hipMemcpyDeviceToHost, st));
-    CHK(hipMemcpyAsync(P.long_ptr_host.data(), lp, (nl + 1) * 8, hipMemcpyDeviceToHost, st));
-    CHK(hipMemcpyAsync(&hf, flags + 1, 4, hipMemcpyDeviceToHost, st));
+    if (nl) CHK(hipMemcpyAsync(P.long_ptr_host.data(), lp, (nl + 1) * 8, hipMemcpyDeviceToHost, st));
+    CHK(hipMemcpyAsync(small, flags, sizeof(small), hipMemcpyDeviceToHost, st));
     CHK(hipStreamSynchronize(st));
+    const int32_t hf = small[1];
     P.slots = P.gp_host[P.ng];
     P.long_nnz = P.long_ptr_host[nl];
     P.perm = (hf & 1) != 0;
@@ -341,6 +372,10 @@ void device_plan(DevPlan &P, const LayoutParams &p, int64_t n_rows, int64_t n_co
     P.lens_s = lens_s;
     P.gp = gp;
     P.long_ptr = lp;
+    if (patterns && !small[4 + 1] && pat_pays(small[4], small[4 + 2], P.slots)) {
+        P.n_pat = small[4];
+        P.pat_stride = small[4 + 2];
+    }
 }
 
 namespace {
@@ -392,6 +427,46 @@ void device_fill(const DevPlan &P, const LayoutParams &p, const int64_t *rp, con
     case RGCSR_BF16: return fill_s<RGCSR_BF16>(vdt, P, p, rp, col, vals, short_len, short_row, slot_val, slot_col, long_row, long_val, long_col, st);
     }
     fail(RGCSR_EINVAL, "bad input dtype");
+}
+
+DevCompact device_compact(DevPlan &P, const LayoutParams &p, int esz, const int64_t *rp, const int32_t *col,
+                          hipStream_t st) {
+    DevCompact C;
+    if (P.n_pat) {
+        C.mode = kCompactPattern;
+        C.n_pat = P.n_pat;
+        C.stride = P.pat_stride;
+        C.width = C.stride - 1;
+        C.rows = compact_rows(C.width, esz);
+        return C;
+    }
+    if (p.G != 64 || P.slots < kWinMinSlots || !win_pays(0, P.slots, P.nnz)) return C;
+    const int32_t rows = compact_rows(P.slots / P.ns, esz), per = kBlockWaves * rows;
+    const int64_t units = (P.ng + per - 1) / per;
+    int32_t *win = (int32_t *)P.scratch.get(2 * units * sizeof(int32_t));
+    unsigned long long *count = (unsigned long long *)P.scratch.get(2 * sizeof(unsigned long long));
+    unsigned long long h[2];
+    CHK(hipMemsetAsync(count, 0, sizeof(h), st));
+    CHK(launch_windows(P.sv, rp, col, P.ns, per * 64, units, win, count, st));
+    CHK(hipMemcpyAsync(h, count, sizeof(h), hipMemcpyDeviceToHost, st));
+    CHK(hipStreamSynchronize(st));
+    if (h[1] > (unsigned long long)kWinCols || !win_pays((int64_t)h[0], P.slots, P.nnz)) return C;
+    C.mode = kCompactWindow;
+    C.rows = rows;
+    C.units = units;
+    C.win = win;
+    return C;
+}
+
+void device_compact_fill(const DevPlan &P, const DevCompact &C, const int64_t *gp, const int32_t *slot_col,
+                         uint8_t *pat_id, int32_t *pat_tab, int32_t *win, uint16_t *col16, hipStream_t st) {
+    if (C.mode == kCompactPattern) {
+        CHK(launch_gather_id(P.sv, P.pat_id, P.ns, pat_id, st));
+        CHK(hipMemcpyAsync(pat_tab, P.pat_tab, (size_t)C.n_pat * C.stride * 4, hipMemcpyDeviceToDevice, st));
+    } else if (C.mode == kCompactWindow) {
+        CHK(hipMemcpyAsync(win, C.win, (size_t)C.units * 8, hipMemcpyDeviceToDevice, st));
+        CHK(launch_col16(gp, P.ng, kBlockWaves * C.rows, C.units, C.win, slot_col, col16, st));
+    }
 }
 
 }  // namespace rg

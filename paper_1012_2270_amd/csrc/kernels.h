@@ -61,6 +61,15 @@ struct SpmvParams {
     int32_t n_map;
     void *pan_y;
     int64_t pan_ld;
+    // compact columns of the grouped rows (compact.h): kCompact* mode, then
+    // row patterns or x windows
+    int32_t compact;
+    int32_t pat_ints, pat_stride;  // table entries, entries per pattern
+    int32_t last_col;              // n_cols - 1
+    const uint8_t *pat_id;         // [ns]
+    const int32_t *pat_tab;        // [pat_ints]
+    const uint16_t *col16;         // [slots]
+    const int32_t *win;            // [2 * units]
     // vectors
     const void *x;
     void *y;
