@@ -14,6 +14,7 @@
 
 #include "compact.h"
 #include "convert.h"
+#include "expand.h"
 #include "internal.h"
 #include "kernels.h"
 #include "tiles.h"
@@ -126,6 +127,19 @@ struct rgcsr_matrix_s {
     void *tile_mem = nullptr;
     size_t tile_bytes = 0;
     std::shared_ptr<HostTiles> pending_tiles;  // host arrays until they are uploaded
+    // two-step SpMV (expand.h), in place of the column tiles where it pays;
+    // its arrays and the expanded x live in exp_mem
+    bool expand = false;
+    void *exp_mem = nullptr;
+    size_t exp_bytes = 0;
+    ExpandPart *exp_parts = nullptr;
+    ExpandRec *exp_recs = nullptr;
+    ExpandWave *exp_waves = nullptr;
+    int32_t *exp_runs = nullptr, *exp_dst = nullptr;
+    uint16_t *exp_lcol = nullptr, *exp_pos = nullptr;
+    void *exp_xg = nullptr;
+    int32_t exp_n_parts = 0, exp_n_waves = 0, exp_block = 0, exp_long = 0, exp_short = 0, exp_max_n = 0, exp_n_runs = 0;
+    std::shared_ptr<HostExpand> pending_expand;  // until the runs are built
     // compact columns of the grouped rows (compact.h)
     int32_t compact = kCompactNone, compact_rows = 1, compact_width = 0, n_pat = 0, pat_stride = 0;
     uint8_t *pat_id = nullptr;
@@ -281,7 +295,7 @@ void add_tile_arrays(rgcsr_matrix_s *h, const HostTiles &T, Arena &a) {
     h->n_rest_wave = (int64_t)T.rest.wave.size();
     h->n_rest_block = (int64_t)T.rest.block.size();
     h->n_rest_combine = (int64_t)T.rest.combine.size();
-    if (!T.active()) return;
+    if (!T.filled()) return;
     a.add(&h->tile_units, T.units.size());
     a.add(&h->tile_ptr, T.ptr.size());
     a.add(&h->tile_lcol, (size_t)T.n_ent);
@@ -297,7 +311,7 @@ void add_tile_arrays(rgcsr_matrix_s *h, const HostTiles &T, Arena &a) {
 // Uploads the tile arrays; values come from the handle's long-row segment
 // (already on the device) through the source map.
 void upload_tiles(rgcsr_matrix_s *h, const HostTiles &T, const std::vector<int32_t> &long_row, hipStream_t st) {
-    if (!T.active()) return;
+    if (!T.filled()) return;
     upload(h->tile_units, T.units, st);
     upload(h->tile_ptr, T.ptr, st);
     upload(h->tile_lcol, T.lcol, st);
@@ -338,12 +352,77 @@ template <class C> void add_compact_arrays(rgcsr_matrix_s *h, const C &c, Arena 
     }
 }
 
+// Units of the two-step SpMV; null where it does not serve the handle: it takes
+// the place of automatic column tiles under the automatic schedule, in
+// device memory of its own, and pays while the (tile, unit) pairs hold enough
+// entries to fill whole runs.
+std::shared_ptr<HostExpand> plan_expand(const rgcsr_matrix_s *h, const HostLayout &L, int32_t rows_per_lane,
+                                        int32_t pad_loads, int32_t load_policy, int32_t tile_min_len) {
+    if (tile_min_len >= 0 || rows_per_lane != 0 || pad_loads >= 0 || load_policy != 0 || h->prm.T != 1 ||
+        h->prm.G != 64)
+        return nullptr;
+    auto X = std::make_shared<HostExpand>();
+    const int64_t cols = expand_cols(h->vdt == RGCSR_F64);
+    X->n_tiles = (h->n_cols + cols - 1) / cols;
+    if (X->n_tiles > kExpandMaxTiles) return nullptr;
+    auto add = [&](int64_t begin, int64_t n, bool is_long, int64_t g0, int64_t g1) {
+        X->max_n = (int32_t)std::max<int64_t>(X->max_n, std::min<int64_t>(n, INT32_MAX));
+        X->units.push_back(ExpandUnit{begin, (int32_t)n, is_long, (int32_t)g0, (int32_t)g1});
+    };
+    for (const LongItem &it : L.work.block) {
+        const int64_t beg = L.long_ptr[it.a] + (int64_t)it.b * kBlockChunk;
+        add(beg, std::min<int64_t>(kExpandUnit, L.long_ptr[it.a + 1] - beg), true, 0, 0);
+    }
+    X->n_block = (int32_t)X->units.size();
+    const int64_t nw = (int64_t)L.work.wave.size();
+    for (int64_t w = 0; w < nw; w += kBlockWaves) {
+        const LongItem &a = L.work.wave[w], &z = L.work.wave[std::min(nw, w + kBlockWaves) - 1];
+        add(L.long_ptr[a.a], L.long_ptr[z.a + z.b] - L.long_ptr[a.a], true, 0, 0);
+    }
+    X->n_long = (int32_t)X->units.size() - X->n_block;
+    X->runs = h->items;
+    if (X->runs.empty()) {
+        // one count everywhere: the same runs, spelled out
+        int32_t lg = 0;
+        while ((1 << lg) < h->R) lg++;
+        for (int64_t g = 0; g < h->ng; g += h->R) X->runs.push_back((int32_t)((g << 2) | lg));
+    }
+    const int64_t nr = (int64_t)X->runs.size();
+    for (int64_t w = 0; w < nr; w += kBlockWaves) {
+        const int32_t z = X->runs[std::min(nr, w + kBlockWaves) - 1];
+        const int64_t g0 = X->runs[w] >> 2, g1 = std::min<int64_t>(h->ng, (int64_t)(z >> 2) + (1 << (z & 3)));
+        add(L.gp[g0], L.group_end(g1 - 1) - L.gp[g0], false, g0, g1);
+    }
+    X->n_short = (int32_t)X->units.size() - X->n_block - X->n_long;
+    for (const LongItem &it : L.work.block) {
+        const int64_t beg = L.long_ptr[it.a] + (int64_t)it.b * kBlockChunk;
+        const int64_t end = std::min(L.long_ptr[it.a + 1], beg + kBlockChunk);
+        X->more.push_back((int32_t)X->units.size());
+        for (int64_t b = beg + kExpandUnit; b < end; b += kExpandUnit)
+            add(b, std::min<int64_t>(kExpandUnit, end - b), true, 0, 0);
+        X->more.push_back((int32_t)X->units.size() - X->more.back());
+    }
+    if (X->max_n > UINT16_MAX - 1 || X->max_n > kExpandUnitBytes / (h->vdt == RGCSR_F64 ? 8 : 4) ||
+        (h->ng > 0 && h->slots == 0) ||  // grouped rows, all of them empty: no slot to read in their place
+        (h->vdt == RGCSR_F64 && h->nnz < kExpandMinNnz64) ||
+        h->nnz < (int64_t)X->units.size() * X->n_tiles * kExpandMinRun ||
+        (int64_t)X->units.size() * X->n_tiles * (kRunLen + 1) + h->nnz > INT32_MAX)
+        return nullptr;
+    return X;
+}
+
+// Builds the runs of a handle whose layout (L: its host sizes, offsets and
+// work items) is on the device.
+void build_expand(rgcsr_matrix_s *h, const HostLayout &L, const HostExpand &X, hipStream_t st);
+
 std::vector<int32_t> panel_unit_map(const rgcsr_matrix_s *h, const HostLayout &L, const PanelBuilt &pb,
                                     bool use_rows);
 
+// own_memory: the handle will allocate its own device memory (a plan's block
+// is sized before there is a device to count the runs on).
 rgcsr_matrix_s *prepare_handle(const HostLayout &L, bool with_row_ptr, const HostLayout *map, Arena &a,
                                int32_t rows_per_lane, int32_t pad_loads, int32_t load_policy, int32_t tile_min_len,
-                               const PanelBuilt *pb = nullptr) {
+                               bool own_memory, const PanelBuilt *pb = nullptr) {
     auto *h = new rgcsr_matrix_s();
     try {
         h->prm = LayoutParams{L.G, L.T, L.sigma, L.tau};
@@ -399,9 +478,12 @@ rgcsr_matrix_s *prepare_handle(const HostLayout &L, bool with_row_ptr, const Hos
         }
         // column tiles: FP64 x for F64 storage, FP32 x otherwise
         auto tiles = std::make_shared<HostTiles>();
-        build_tiles(L, tile_min_len, *tiles);
+        select_tiles(L, tile_min_len, nullptr, *tiles);
+        if (tiles->active() && own_memory)
+            h->pending_expand = plan_expand(h, L, rows_per_lane, pad_loads, load_policy, tile_min_len);
+        if (!h->pending_expand) fill_tiles(L, *tiles);
         add_tile_arrays(h, *tiles, a);
-        if (tiles->active()) h->pending_tiles = tiles;
+        if (tiles->filled()) h->pending_tiles = tiles;
         // (a panel copy serves several right-hand sides over random columns)
         if (!pb && compact_wanted(h->prm, rows_per_lane, pad_loads, load_policy)) {
             auto C = std::make_shared<HostCompact>();
@@ -489,12 +571,15 @@ rgcsr_matrix_s *make_device(const HostLayout &L, const std::vector<int64_t> *row
                             const PanelBuilt *pb = nullptr) {
     Arena a;
     rgcsr_matrix_s *h = prepare_handle(L, row_ptr != nullptr, map, a, rows_per_lane, pad_loads, load_policy,
-                                       tile_min_len, pb);
+                                       tile_min_len, true, pb);
     try {
         place_and_upload(h, a, L, row_ptr, map, nullptr, st);
+        if (h->pending_expand) build_expand(h, L, *h->pending_expand, st);
+        h->pending_expand.reset();
     } catch (...) {
         (void)hipStreamSynchronize(st);
         if (h->mem && h->owns_mem) (void)hipFree(h->mem);
+        if (h->exp_mem) (void)hipFree(h->exp_mem);
         delete h;
         throw;
     }
@@ -574,31 +659,48 @@ rgcsr_matrix_s *make_device_on_device(DevPlan &P, const LayoutParams &p, int vdt
         if (keep_map)
             HIPCHK(hipMemcpyAsync(h->row_ptr, rp, ((size_t)P.n_rows + 1) * 8, hipMemcpyDeviceToDevice, st));
         HIPCHK(hipStreamSynchronize(st));
-        // column tiles from the converted long-row segment: its columns come
-        // back to the host, the tile arrays go to a block of their own
+        // column tiles, or the two-step SpMV in their place, from the converted
+        // long-row segment; the rows that no unit may hold are told apart on
+        // the device (they lead the list, longest first)
         if (tile_min_len != 0 && L.nl > 0) {
-            L.nl = P.nl;
             L.long_ptr = P.long_ptr_host;
-            L.long_col.resize((size_t)L.long_nnz);
-            L.long_row.resize((size_t)L.nl);
-            if (L.long_nnz)
-                HIPCHK(hipMemcpyAsync(L.long_col.data(), h->long_col, (size_t)L.long_nnz * 4, hipMemcpyDeviceToHost, st));
-            HIPCHK(hipMemcpyAsync(L.long_row.data(), h->long_row, (size_t)L.nl * 4, hipMemcpyDeviceToHost, st));
-            HIPCHK(hipStreamSynchronize(st));
+            const int64_t um = tile_unit_max(vdt);
+            int64_t nd = 0;
+            while (nd < L.nl && L.long_ptr[nd + 1] - L.long_ptr[nd] > um) nd++;
+            std::vector<uint8_t> dense((size_t)L.nl, 0);
+            if (nd) {
+                uint8_t *d = (uint8_t *)P.scratch.get((size_t)nd);
+                HIPCHK(launch_tile_dense(h->long_ptr, h->long_col, nd, vdt, d, st));
+                HIPCHK(hipMemcpyAsync(dense.data(), d, (size_t)nd, hipMemcpyDeviceToHost, st));
+                HIPCHK(hipStreamSynchronize(st));
+            }
             HostTiles T;
-            build_tiles(L, tile_min_len, T);
+            select_tiles(L, tile_min_len, &dense, T);
+            std::shared_ptr<HostExpand> X;
+            if (T.active()) X = plan_expand(h, L, rows_per_lane, pad_loads, load_policy, tile_min_len);
+            if (T.active() && !X) {
+                // their arrays are built on the host and go to a block of their own
+                L.long_col.resize((size_t)L.long_nnz);
+                L.long_row.resize((size_t)L.nl);
+                HIPCHK(hipMemcpyAsync(L.long_col.data(), h->long_col, (size_t)L.long_nnz * 4, hipMemcpyDeviceToHost, st));
+                HIPCHK(hipMemcpyAsync(L.long_row.data(), h->long_row, (size_t)L.nl * 4, hipMemcpyDeviceToHost, st));
+                HIPCHK(hipStreamSynchronize(st));
+                fill_tiles(L, T);
+            }
             Arena ta;
             add_tile_arrays(h, T, ta);
-            if (T.active()) {
+            if (T.filled()) {
                 h->tile_mem = ta.commit();
                 h->tile_bytes = ta.total;
                 upload_tiles(h, T, L.long_row, st);
             }
+            if (X) build_expand(h, L, *X, st);
         }
     } catch (...) {
         (void)hipStreamSynchronize(st);
         if (h->mem) (void)hipFree(h->mem);
         if (h->tile_mem) (void)hipFree(h->tile_mem);
+        if (h->exp_mem) (void)hipFree(h->exp_mem);
         delete h;
         throw;
     }
@@ -611,13 +713,14 @@ void free_handle(rgcsr_matrix_s *h) {
     if (h->PN) free_handle(h->PN);
     if (h->mem && h->owns_mem) (void)hipFree(h->mem);
     if (h->tile_mem) (void)hipFree(h->tile_mem);
+    if (h->exp_mem) (void)hipFree(h->exp_mem);
     delete h;
 }
 
 // Device memory that freeing the handle releases (none for a handle built
 // into caller memory: its transpose sits in the same block).
 bool owns_device_memory(const rgcsr_matrix_s *h) {
-    return h && ((h->mem && h->owns_mem) || h->tile_mem || owns_device_memory(h->AT) || owns_device_memory(h->PN));
+    return h && ((h->mem && h->owns_mem) || h->tile_mem || h->exp_mem || owns_device_memory(h->AT) || owns_device_memory(h->PN));
 }
 
 void check_handle(const rgcsr_matrix_s *h) {
@@ -701,8 +804,8 @@ SpmvParams params_of(const rgcsr_matrix_s *h, bool use_rows, bool tiled = false)
     P.compact = h->compact;
     P.pat_ints = h->n_pat * h->pat_stride; P.pat_stride = h->pat_stride; P.last_col = (int32_t)(h->n_cols - 1);
     P.pat_id = h->pat_id; P.pat_tab = h->pat_tab; P.col16 = h->col16; P.win = h->win;
-    P.tile_dst = h->n_tent ? h->tile_dst : nullptr;
-    P.tile_vals = h->n_tent ? h->tile_val : nullptr;
+    P.tile_dst = h->tile_dst;
+    P.tile_vals = h->tile_val;
     int64_t n_block = h->n_block, n_wave_long = h->n_wave_long, n_comb = 0;
     if (tiled) {
         P.wave_work = h->rest_wave;
@@ -730,6 +833,90 @@ SpmvParams params_of(const rgcsr_matrix_s *h, bool use_rows, bool tiled = false)
     P.n_long_waves = (int32_t)h->nl;
     P.total_waves = (int32_t)tot;
     return P;
+}
+
+void build_expand(rgcsr_matrix_s *h, const HostLayout &L, const HostExpand &X, hipStream_t st) {
+    const int f64 = h->vdt == RGCSR_F64;
+    const int32_t nu = (int32_t)X.units.size(), nt = (int32_t)X.n_tiles;
+    const int64_t pairs = (int64_t)nu * nt;
+    const SpmvParams P = params_of(h, true);
+    size_t scan_bytes = 0;
+    HIPCHK(expand_scan_bytes(pairs, &scan_bytes));
+    DevScratch S;
+    S.st = st;
+    S.reserve((size_t)pairs * 16 + (size_t)nu * (sizeof(ExpandUnit) + 4) + (size_t)nt * 4 + scan_bytes + 8192);
+    ExpandUnit *units = (ExpandUnit *)S.get((size_t)nu * sizeof(ExpandUnit));
+    int32_t *cnt = (int32_t *)S.get(pairs * 4), *cnt_t = (int32_t *)S.get(pairs * 4);
+    int32_t *by_unit = (int32_t *)S.get(pairs * 4), *by_tile = (int32_t *)S.get(pairs * 4);
+    int32_t *ptrs = (int32_t *)S.get(((size_t)nu + nt + 2) * 4);  // units, then tiles
+    void *temp = S.get(scan_bytes);
+    upload(units, X.units, st);
+    HIPCHK(launch_expand_count(P, units, nu, f64, nt, cnt, cnt_t, st));
+    HIPCHK(launch_expand_scan(cnt, by_unit, pairs, temp, scan_bytes, st));
+    HIPCHK(launch_expand_scan(cnt_t, by_tile, pairs, temp, scan_bytes, st));
+    HIPCHK(launch_expand_ptrs(by_unit, nt, nu, by_unit + pairs - 1, cnt + pairs - 1, ptrs, st));
+    HIPCHK(launch_expand_ptrs(by_tile, nu, nt, by_tile + pairs - 1, cnt_t + pairs - 1, ptrs + nu + 1, st));
+    std::vector<int32_t> hp((size_t)nu + nt + 2);
+    HIPCHK(hipMemcpyAsync(hp.data(), ptrs, hp.size() * 4, hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    const int64_t runs = hp[nu];
+    // the expand workgroups: one per CU (each holds its tile for as many
+    // entries as possible; two per CU 14.5 against 13.5 us), fewer where one
+    // would stream fewer entries than the tile it holds; part p of tile t goes to workgroup
+    // p * t8 + t, so a tile stays on one XCD (workgroup b runs on XCD b % 8)
+    const int32_t *tp = hp.data() + nu + 1;
+    const int64_t t8 = ((int64_t)nt + 7) / 8 * 8;
+    const int64_t split = std::max<int64_t>(
+        1, std::min<int64_t>((int64_t)cu_count(h->device) / t8, runs * kRunLen / (4096 * t8)));
+    std::vector<ExpandPart> parts((size_t)(t8 * split), ExpandPart{0, 0, -1});
+    for (int64_t t = 0; t < nt; t++)
+        for (int64_t p = 0; p < split; p++) {
+            const int64_t n = tp[t + 1] - tp[t], a = tp[t] + n * p / split, z = tp[t] + n * (p + 1) / split;
+            if (z > a) parts[p * t8 + t] = ExpandPart{a * kRunLen, (int32_t)((z - a) * kRunLen), (int32_t)t};
+        }
+    std::vector<ExpandRec> recs((size_t)nu);
+    for (int32_t u = 0; u < nu; u++) {
+        ExpandRec &r = recs[u];
+        r.begin = X.units[u].begin;
+        r.e0 = (int64_t)hp[u] * kRunLen;
+        r.n = X.units[u].n;
+        r.n_pad = (hp[u + 1] - hp[u]) * kRunLen;
+        r.next = u < X.n_block ? X.more[2 * u] : 0;
+        r.count = u < X.n_block ? X.more[2 * u + 1] : 0;
+    }
+    std::vector<ExpandWave> waves(L.work.wave.size());
+    for (size_t w = 0; w < waves.size(); w++) {
+        const LongItem &it = L.work.wave[w];
+        const int64_t at = L.long_ptr[it.a], begin = L.long_ptr[L.work.wave[w / kBlockWaves * kBlockWaves].a];
+        waves[w] = ExpandWave{(int32_t)(at - begin), (int32_t)(L.long_ptr[it.a + it.b] - at), it.a, (int16_t)it.b,
+                              (int16_t)it.c};
+    }
+    Arena a;
+    a.add(&h->exp_parts, parts.size());
+    a.add(&h->exp_recs, recs.size());
+    a.add(&h->exp_waves, waves.size());
+    a.add(&h->exp_runs, X.runs.size());
+    // (a spare run each, read and not used by passes past the last entry)
+    a.add(&h->exp_dst, (size_t)runs + 1);
+    a.add(&h->exp_lcol, ((size_t)runs + 1) * kRunLen);
+    a.add(&h->exp_pos, ((size_t)runs + 1) * kRunLen);
+    a.add((uint8_t **)&h->exp_xg, ((size_t)runs + 1) * kRunLen * (f64 ? 8 : 4));
+    h->exp_mem = a.commit();
+    h->exp_bytes = a.total;
+    upload(h->exp_parts, parts, st);
+    upload(h->exp_recs, recs, st);
+    upload(h->exp_waves, waves, st);
+    upload(h->exp_runs, X.runs, st);
+    HIPCHK(launch_expand_fill(P, units, nu, f64, nt, by_unit, by_tile, h->exp_lcol, h->exp_dst, h->exp_pos, st));
+    h->exp_n_parts = (int32_t)parts.size();
+    h->exp_n_waves = (int32_t)waves.size();
+    h->exp_n_runs = (int32_t)X.runs.size();
+    h->exp_block = X.n_block;
+    h->exp_long = X.n_long;
+    h->exp_short = X.n_short;
+    h->exp_max_n = X.max_n;
+    HIPCHK(hipStreamSynchronize(st));
+    h->expand = true;
 }
 
 int vec_is_f64(rgcsr_dtype vt) {
@@ -766,7 +953,8 @@ void spmv_launch(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx, voi
     const rgcsr_matrix_s *src = panels ? pn : h;
     const bool rows = K == 1 || (K * (f64 ? 8 : 4) <= kRunsRowBytes && src->R == 0);
     const int32_t R = K == 1 ? src->R : (rows ? 0 : 1);
-    SpmvParams P = params_of(src, rows, tiled);
+    const bool expand = tiled && h->expand;
+    SpmvParams P = params_of(src, rows, tiled && !expand);
     P.x = X; P.y = Y; P.ldx = ldx; P.ldy = ldy;
     int64_t nwg = P.total_units;
     if (panels) {
@@ -805,6 +993,25 @@ void spmv_launch(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx, voi
         }
         e = launch_panel_combine(pn->pan_crow, pn->pan_cptr, pn->n_split, pn->pan_vidx, pn->pan_y, Y, ldy, f64, K, st);
         if (e != hipSuccess) fail(RGCSR_EHIP, std::string("panel combine launch: ") + hipGetErrorString(e));
+        return;
+    }
+    if (expand) {
+        ExpandParams E{};
+        E.P = P;
+        E.parts = h->exp_parts; E.n_parts = h->exp_n_parts;
+        E.lcol = h->exp_lcol; E.dst = h->exp_dst; E.pos = h->exp_pos; E.xg = h->exp_xg;
+        E.recs = h->exp_recs;
+        E.waves = h->exp_waves; E.n_waves = h->exp_n_waves;
+        E.runs = h->exp_runs; E.n_runs = h->exp_n_runs;
+        E.n_block = h->exp_block; E.n_long = h->exp_long; E.n_short = h->exp_short; E.max_n = h->exp_max_n;
+        E.x_aligned = ((uintptr_t)X % 16) == 0;
+        e = launch_expand(E, vd, st);
+        if (e == hipSuccess) e = launch_expand_spmv(E, vd, st);
+        if (e != hipSuccess) fail(RGCSR_EHIP, std::string("two-step launch: ") + hipGetErrorString(e));
+        if (h->n_combine) {
+            e = launch_combine(h->combine, (int32_t)h->n_combine, h->long_row, h->partial, Y, ldy, nullptr, 0, f64, K, st);
+            if (e != hipSuccess) fail(RGCSR_EHIP, std::string("combine launch: ") + hipGetErrorString(e));
+        }
         return;
     }
     if (tiled) {
@@ -968,10 +1175,10 @@ rgcsr_plan plan_of(int32_t count, const int64_t *n_rows, const int64_t *n_cols, 
     build_host(P->B, p, o.value_dtype, count, n_rows, n_cols, row_ptr, col_idx, vals, vals_dtype, o.validate != 0,
                o.keep_csr_map != 0, tr);
     P->h = prepare_handle(P->B.L, P->with_row_ptr, nullptr, P->a, o.rows_per_lane, o.pad_loads, o.load_policy,
-                          o.tile_min_len);
+                          o.tile_min_len, false);
     if (tr)
         P->hT = prepare_handle(P->B.LT, false, &P->B.LTmap, P->aT, o.rows_per_lane, o.pad_loads, o.load_policy,
-                               o.tile_min_len);
+                               o.tile_min_len, false);
     return P.release();
 }
 
@@ -1203,7 +1410,7 @@ rgcsr_status rgcsr_set_values(rgcsr_handle A, const void *vals, rgcsr_dtype vals
             hipError_t e = launch_gather_map(A->AT->slots, A->vdt, A->AT->t_map_slot, theta, theta_f64, A->AT->slot_val, st);
             if (e == hipSuccess)
                 e = launch_gather_map(A->AT->long_nnz, A->vdt, A->AT->t_map_long, theta, theta_f64, A->AT->long_val, st);
-            if (e == hipSuccess && A->AT->n_tent)
+            if (e == hipSuccess && A->AT->tile_dst)
                 e = launch_tile_values(A->AT->long_nnz, A->AT->tile_dst, A->AT->long_val, A->AT->tile_val, A->esz, st);
             if (e != hipSuccess) fail(RGCSR_EHIP, std::string("set_values (transpose): ") + hipGetErrorString(e));
         }
@@ -1312,7 +1519,7 @@ rgcsr_status rgcsr_info(rgcsr_handle A, rgcsr_info_t *out) {
     out->rows_per_lane = A->R;
     out->pad_loads = A->pad;
     out->load_policy = A->lp;
-    out->device_bytes += (int64_t)A->tile_bytes + (A->AT ? (int64_t)A->AT->tile_bytes : 0);
+    out->device_bytes += (int64_t)(A->tile_bytes + A->exp_bytes) + (A->AT ? (int64_t)(A->AT->tile_bytes + A->AT->exp_bytes) : 0);
     out->tiled_rows = A->n_trows;
     out->tile_entries = A->n_tent;
     out->n_tiles = A->n_tiles;
@@ -1347,6 +1554,7 @@ rgcsr_matrix_s *clone_handle(const rgcsr_matrix_s *A, hipStream_t st) {
     h->AT = nullptr;
     h->PN = nullptr;
     h->tile_mem = nullptr;
+    h->exp_mem = nullptr;
     try {
         if (A->bytes) HIPCHK(hipMalloc(&h->mem, A->bytes));
         if (A->bytes) HIPCHK(hipMemcpyAsync(h->mem, A->mem, A->bytes, hipMemcpyDeviceToDevice, st));
@@ -1376,6 +1584,13 @@ rgcsr_matrix_s *clone_handle(const rgcsr_matrix_s *A, hipStream_t st) {
             tile_rebase(&rgcsr_matrix_s::tile_mem);
         } else {
             tile_rebase(&rgcsr_matrix_s::mem);
+        }
+        if (A->exp_mem) {
+            HIPCHK(hipMalloc(&h->exp_mem, A->exp_bytes));
+            HIPCHK(hipMemcpyAsync(h->exp_mem, A->exp_mem, A->exp_bytes, hipMemcpyDeviceToDevice, st));
+            rebase(h, A, &rgcsr_matrix_s::exp_mem, &rgcsr_matrix_s::exp_parts, &rgcsr_matrix_s::exp_recs,
+                   &rgcsr_matrix_s::exp_waves, &rgcsr_matrix_s::exp_runs, &rgcsr_matrix_s::exp_dst,
+                   &rgcsr_matrix_s::exp_lcol, &rgcsr_matrix_s::exp_pos, &rgcsr_matrix_s::exp_xg);
         }
         if (A->AT) h->AT = clone_handle(A->AT, st);
         if (A->PN) h->PN = clone_handle(A->PN, st);

@@ -18,6 +18,17 @@ namespace rg {
 // or the x window, its rows' metadata, the values (and 16-bit columns) of the
 // first pass -- is loaded before anything waits: one memory latency, then one
 // for the gathers of a pattern (an x window has none, it gathers from LDS).
+//
+// Bound by the value stream (patterns: 7-point 128^3 FP32 77 MB instead of
+// 134, 23.5 -> 14.4 us, 5.4 TB/s; 27-point 101^3 FP64 238 MB instead of 344,
+// 64.5 -> 48.0 us) and, where the columns are random in a band, by the x
+// gathers: one touches about 28 cache lines, so gathering from LDS counts for
+// more than the two bytes saved (400,009 rows of 24 nonzeros, half band 500,
+// BF16: 20.0 -> 11.4 us; with the 16-bit columns alone 18.9).
+// Tried and slower: a resident grid that walks the units and prefetches the
+// next pass's values (7-point 16.6-23 us, 27-point FP64 53-60), prefetching
+// the next pass within a unit (windows 13.6 us), the table behind a barrier
+// before the first loads (7-point 15.6 us).
 // ---------------------------------------------------------------------------
 
 // The R groups of one wavefront: metadata of each lane's rows, and the first

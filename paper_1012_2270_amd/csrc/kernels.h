@@ -137,6 +137,9 @@ struct TileParams {
     int32_t n_trows;
     int32_t x_aligned;       // x is 16-byte aligned (vector loads of a tile)
 };
+// dense[i] = tile_dense_row of long row i, i < n
+hipError_t launch_tile_dense(const int64_t *long_ptr, const int32_t *long_col, int64_t n, int vdt, uint8_t *dense,
+                             hipStream_t st);
 hipError_t launch_tile_spmv(const TileParams &P, int vdt, int n_units, hipStream_t st);
 // tile_val[dst[q]] = long_val[q] for the n long-row elements whose row is
 // tiled (dst[q] >= 0)

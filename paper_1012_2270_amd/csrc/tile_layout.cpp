@@ -51,7 +51,16 @@ void build_long_work_except(const std::vector<int64_t> &long_ptr, const std::vec
     }
 }
 
-void build_tiles(const HostLayout &L, int64_t min_len, HostTiles &T) {
+bool tile_dense_row(const int32_t *col, int64_t n, int vdt) {
+    // columns ascend, so a segment of more than UM entries holds two entries
+    // UM apart
+    const int64_t C = tile_cols(vdt), UM = tile_unit_max(vdt);
+    for (int64_t q = 0; q + UM < n; q++)
+        if (col[q] / C == col[q + UM] / C) return true;
+    return false;
+}
+
+void select_tiles(const HostLayout &L, int64_t min_len, const std::vector<uint8_t> *dense, HostTiles &T) {
     T = HostTiles{};
     if (min_len == 0 || L.nl == 0 || L.n_cols == 0) return;
     const bool automatic = min_len < 0;
@@ -59,24 +68,14 @@ void build_tiles(const HostLayout &L, int64_t min_len, HostTiles &T) {
     const int64_t UM = tile_unit_max(L.vdt);
     const int64_t n_tiles = (L.n_cols + C - 1) / C;
     const int64_t thr = std::max<int64_t>(automatic ? 256 : min_len, (n_tiles + 1) / 2);
-    // a row's segment in one tile must fit a unit: a row with more than UM
-    // entries in some tile stays on the long-row path (columns
-    // ascend within a row, so a segment is a run of consecutive entries)
-    auto longest_segment = [&](int64_t i) {
-        int64_t best = 0, run = 0, prev = -1;
-        for (int64_t q = L.long_ptr[i]; q < L.long_ptr[i + 1]; q++) {
-            const int64_t t = L.long_col[q] / C;
-            run = t == prev ? run + 1 : 1;
-            prev = t;
-            best = std::max(best, run);
-        }
-        return best;
-    };
     T.tiled.assign(L.nl, 0);
     int64_t n_ent = 0;
     for (int64_t i = 0; i < L.nl; i++) {
         const int64_t len = L.long_ptr[i + 1] - L.long_ptr[i];
-        if (len < thr || (len > UM && longest_segment(i) > UM)) continue;
+        if (len < thr) continue;
+        // a row's segment in one tile must fit a unit: a row with more than UM
+        // entries in some tile stays on the long-row path
+        if (len > UM && (dense ? (*dense)[i] != 0 : tile_dense_row(&L.long_col[L.long_ptr[i]], len, L.vdt))) continue;
         T.tiled[i] = 1;
         T.trow.push_back((int32_t)i);
         n_ent += len;
@@ -90,6 +89,13 @@ void build_tiles(const HostLayout &L, int64_t min_len, HostTiles &T) {
     T.n_trows = (int64_t)T.trow.size();
     T.n_ent = n_ent;
     T.min_len = thr;
+}
+
+void fill_tiles(const HostLayout &L, HostTiles &T) {
+    if (!T.active()) return;
+    const int64_t C = tile_cols(L.vdt);
+    const int64_t UM = tile_unit_max(L.vdt);
+    const int64_t n_tiles = T.n_tiles, n_ent = T.n_ent;
     const int64_t nt = T.n_trows;
     // counts per (tile, row), then tile-major offsets
     T.ptr.assign(n_tiles * (nt + 1), 0);
@@ -169,6 +175,11 @@ void build_tiles(const HostLayout &L, int64_t min_len, HostTiles &T) {
         for (int x = 0; x < 8; x++) T.units.push_back(d < q[x].size() ? q[x][d] : TileUnit{-1, 0, 0, 1, 0, 0});
     while (!T.units.empty() && T.units.back().t < 0) T.units.pop_back();
     build_long_work_except(L.long_ptr, T.tiled, T.rest);
+}
+
+void build_tiles(const HostLayout &L, int64_t min_len, HostTiles &T) {
+    select_tiles(L, min_len, nullptr, T);
+    fill_tiles(L, T);
 }
 
 }  // namespace rg

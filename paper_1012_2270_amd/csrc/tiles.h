@@ -54,16 +54,25 @@ struct HostTiles {
     std::vector<uint8_t> tiled;        // [nl] 1 when long row i is tiled
     LongWork rest;                     // long-row work of the rows that are not tiled
     bool active() const { return n_trows > 0; }
+    bool filled() const { return !ptr.empty(); }
 };
 
 // Selects the tiled rows of layout L (long rows of at least
 // max(min_len, tiles / 2) nonzeros, so the partial sums never outnumber the
 // entries twice over, and at most tile_unit_max(vdt) nonzeros in any one
-// tile, so a row's segment fits a unit;
-// min_len < 0 picks 256 and keeps the tiles only when they hold at least
-// kTileMinEntries entries; 0 disables) and builds their index arrays and
-// units (values are copied on the device through src).  Needs L.long_ptr and
-// L.long_col.
+// tile, so a row's segment fits a unit; min_len < 0 picks 256 and keeps the
+// tiles only when they hold at least kTileMinEntries entries; 0 disables):
+// the counts, trow and tiled of T.  Needs L.long_ptr, and L.long_col unless
+// dense tells for each long row of more than tile_unit_max(vdt) nonzeros
+// whether some tile holds more than that of them (tile_dense_row).
+void select_tiles(const HostLayout &L, int64_t min_len, const std::vector<uint8_t> *dense, HostTiles &T);
+bool tile_dense_row(const int32_t *col, int64_t n, int vdt);
+
+// Builds the index arrays and units of the selected rows (values are copied
+// on the device through src).  Needs L.long_ptr and L.long_col.
+void fill_tiles(const HostLayout &L, HostTiles &T);
+
+// Both.
 void build_tiles(const HostLayout &L, int64_t min_len, HostTiles &T);
 
 // Long-row work items of the rows not tiled (the tiled ones skipped).

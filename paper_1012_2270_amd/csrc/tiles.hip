@@ -127,6 +127,24 @@ hipError_t launch_tile_spmv(const TileParams &P, int vdt, int n_units, hipStream
     return hipGetLastError();
 }
 
+// tile_dense_row of the first n long rows, one workgroup per row
+__global__ __launch_bounds__(256) void tile_dense_k(const int64_t *long_ptr, const int32_t *long_col, int32_t cols,
+                                                    int32_t um, uint8_t *dense) {
+    const int64_t b = long_ptr[blockIdx.x], e = long_ptr[blockIdx.x + 1];
+    bool d = false;
+    for (int64_t q = b + threadIdx.x; q + um < e; q += 256) d = d || long_col[q] / cols == long_col[q + um] / cols;
+    const int any = __syncthreads_or(d);
+    if (threadIdx.x == 0) dense[blockIdx.x] = any != 0;
+}
+
+hipError_t launch_tile_dense(const int64_t *long_ptr, const int32_t *long_col, int64_t n, int vdt, uint8_t *dense,
+                             hipStream_t st) {
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(tile_dense_k, dim3((unsigned)n), dim3(256), 0, st, long_ptr, long_col, tile_cols(vdt),
+                       tile_unit_max(vdt), dense);
+    return hipGetLastError();
+}
+
 template <class E>
 __global__ __launch_bounds__(256) void tile_values_k(int64_t n, const int32_t *dst, const E *lv, E *tv) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
