@@ -321,10 +321,10 @@ rgcsr_status rgcsr_spmv(rgcsr_handle A, const void *x, void *y, rgcsr_dtype vec_
 /* rgcsr_spmv_batched: Y = A X for k right-hand sides.  X is n_cols x k
  * row-major with leading dimension ldx >= k, Y is n_rows x k with ldy >= k
  * (device pointers, elements of vec_dtype).  For a batch handle this is
- * Y_m = A_m X_m for every matrix m.  k in {1, 2, 4, 8, 16, 32} runs as one
- * launch when X and Y are 16-byte aligned with ldx, ldy multiples of 4 (F32)
- * or 2 (F64); other k, or unaligned blocks, run as several launches over
- * column blocks (narrower blocks read X and Y rows with scalar accesses).
+ * Y_m = A_m X_m for every matrix m.  Any k up to 32 runs as one launch, X and
+ * Y at any element alignment and with any ldx and ldy; more columns run as
+ * launches of equal width.  (A second small launch adds chunk partial sums of
+ * rows over 16,384 nonzeros.)
  * Handles with lanes_per_row > 1 or F16/BF16 stored values run one
  * single-column launch per column.  persistent = 1 launches a fixed grid of
  * wavefronts that loop over the work items (one resident launch); 0 launches

@@ -17,6 +17,7 @@
 #include "expand.h"
 #include "internal.h"
 #include "kernels.h"
+#include "spmm.h"
 #include "tiles.h"
 
 namespace rg {
@@ -934,24 +935,40 @@ int vec_is_f64(rgcsr_dtype vt) {
 bool panel_slice_ok(const rgcsr_matrix_s *h, int64_t ldx, int f64) {
     return h->PN && h->PN->panel_cols * ldx * (f64 ? 8 : 4) <= kPanelSliceBytes;
 }
-bool panel_launch_ok(const rgcsr_matrix_s *h, int K, int64_t ldx, int f64) {
-    return K > 1 && panel_slice_ok(h, ldx, f64) && K * (f64 ? 8 : 4) <= kPanelRowBytes;
+// (its kernels, one lane per row, are compiled for 2, 4 and 8 columns and read
+// and write rows of whole 16-byte vectors with vector accesses)
+bool lane_kernel_ok(int K, const void *X, int64_t ldx, const void *Y, int64_t ldy, int f64) {
+    const int vw = f64 ? 2 : 4;
+    const bool aligned = (uintptr_t)X % 16 == 0 && (uintptr_t)Y % 16 == 0 && ldx % vw == 0 && ldy % vw == 0;
+    return (K == 2 || K == 4 || (K == 8 && !f64)) && (K % vw != 0 || aligned);
+}
+bool panel_launch_ok(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx, const void *Y, int64_t ldy, int f64) {
+    return lane_kernel_ok(K, X, ldx, Y, ldy, f64) && panel_slice_ok(h, ldx, f64) && K * (f64 ? 8 : 4) <= kPanelRowBytes;
+}
+// On the layout one lane per row stays for rows of X of at most 16 bytes,
+// which it reads in one load, unless row patterns give the columns (Zipf 10^6,
+// k = 2 and 4: 80.6 and 106.8 us against 111 and 124 with lanes sharing rows;
+// 27-point 80^3 with patterns: 25.4 and 28.1 against 19.5 and 21.9).
+bool narrow_launch_ok(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx, const void *Y, int64_t ldy, int f64) {
+    return lane_kernel_ok(K, X, ldx, Y, ldy, f64) && K * (f64 ? 8 : 4) <= kRunsRowBytes && h->compact != kCompactPattern;
 }
 
 void spmv_launch(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx, void *Y, int64_t ldy, int f64,
                  bool persistent, hipStream_t st) {
     if (h->n_rows == 0) return;
-    const bool panels = panel_launch_ok(h, K, ldx, f64);
+    const bool panels = panel_launch_ok(h, K, X, ldx, Y, ldy, f64);
     const rgcsr_matrix_s *pn = h->PN;
     // the column-tiled rows take one vector with unit stride (FP64 for F64
     // storage, FP32 otherwise) and the default load policy; everything else
     // runs them on the long-row path
     const bool tiled = !panels && h->n_trows > 0 && K == 1 && (f64 != 0) == (h->vdt == RGCSR_F64) && ldx == 1 &&
                        h->lp == 0;
-    // right-hand sides of up to kRunsRowBytes per row take the runs of rows
-    // per lane (R = 0) when the handle has them; otherwise one row per lane
+    // with one lane per row, right-hand sides of up to kRunsRowBytes per row take
+    // the runs of rows per lane (R = 0) when the handle has them; otherwise one
+    // row per lane
+    const bool narrow = !panels && K > 1 && narrow_launch_ok(h, K, X, ldx, Y, ldy, f64);
     const rgcsr_matrix_s *src = panels ? pn : h;
-    const bool rows = K == 1 || (K * (f64 ? 8 : 4) <= kRunsRowBytes && src->R == 0);
+    const bool rows = K == 1 || ((panels || narrow) && K * (f64 ? 8 : 4) <= kRunsRowBytes && src->R == 0);
     const int32_t R = K == 1 ? src->R : (rows ? 0 : 1);
     const bool expand = tiled && h->expand;
     SpmvParams P = params_of(src, rows, tiled && !expand);
@@ -993,6 +1010,12 @@ void spmv_launch(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx, voi
         }
         e = launch_panel_combine(pn->pan_crow, pn->pan_cptr, pn->n_split, pn->pan_vidx, pn->pan_y, Y, ldy, f64, K, st);
         if (e != hipSuccess) fail(RGCSR_EHIP, std::string("panel combine launch: ") + hipGetErrorString(e));
+        return;
+    }
+    if (K > 1 && !narrow) {
+        e = launch_spmm(P, vd, f64, K, (int)nwg, st);
+        if (e == hipSuccess) e = launch_spmm_combine(h->combine, (int32_t)h->n_combine, h->long_row, h->partial, Y, ldy, f64, K, st);
+        if (e != hipSuccess) fail(RGCSR_EHIP, std::string("spmm launch: ") + hipGetErrorString(e));
         return;
     }
     if (expand) {
@@ -1323,29 +1346,24 @@ rgcsr_status rgcsr_spmv_batched(rgcsr_handle A, int32_t k, const void *X, int64_
     if (ldx < k || ldy < k) fail(RGCSR_EINVAL, "ldx and ldy must be >= k");
     if ((!X && A->n_cols) || (!Y && A->n_rows)) fail(RGCSR_EINVAL, "null vector");
     const int f64 = vec_is_f64(vec_dtype);
-    const int esz = f64 ? 8 : 4, vw = f64 ? 2 : 4;
-    // Column blocks of 32, 16, 8, 4, 2, 1.  Blocks whose width is a multiple of
-    // the 16-byte vector width read X and Y rows with vector accesses, which
-    // needs 16-byte aligned rows; otherwise narrower blocks (scalar accesses)
-    // are used.
-    const bool aligned = ((uintptr_t)X % 16 == 0) && ((uintptr_t)Y % 16 == 0) && (ldx % vw == 0) && (ldy % vw == 0);
+    const int esz = f64 ? 8 : 4;
     // the multi-column kernels take one lane per row and F32/F64 values;
     // other handles run one single-column launch per column (strided x, y)
     const bool blocks = A->prm.T == 1 && (A->vdt == RGCSR_F32 || A->vdt == RGCSR_F64);
-    // a panel copy takes column blocks whose sums fit its piece buffer
-    const int32_t kmax = panel_slice_ok(A, ldx, f64) ? kPanelRowBytes / esz : 32;
     int32_t done = 0;
     while (done < k) {
-        int32_t kb = 1;
-        for (int32_t c : {32, 16, 8, 4, 2, 1}) {
-            if (!blocks) break;
-            if (c > k - done || c > kmax) continue;
-            if (c % vw == 0 && (!aligned || ((size_t)done * esz) % 16 != 0)) continue;
-            kb = c;
-            break;
-        }
         const char *xp = (const char *)X + (size_t)done * esz;
         char *yp = (char *)Y + (size_t)done * esz;
+        const int32_t left = k - done;
+        int32_t kb = 1;
+        if (blocks) {
+            // one launch, or as few of equal width as kSpmmMax columns each
+            // allow (a panel copy serves widths of its own kernels only: three
+            // columns in two launches on it take 170 us, in one on the layout
+            // 125; twelve 216 and 172)
+            const int32_t n = (left + kSpmmMax - 1) / kSpmmMax;
+            kb = (left + n - 1) / n;
+        }
         spmv_launch(A, kb, xp, ldx, yp, ldy, f64, persistent != 0, (hipStream_t)stream);
         done += kb;
     }

@@ -152,6 +152,63 @@ __device__ __forceinline__ GroupMeta group_meta_uniform(const SpmvParams &P, int
     return m;
 }
 
+// Geometry of the row a lane owns in the grouped part.
+struct LaneRow {
+    int64_t i;       // index into short_len / short_row
+    int64_t base;    // first slot of this lane
+    int64_t stride;  // slots between this lane's consecutive elements
+    int len;         // row length
+    int q;           // sub-lane within the row (0 .. T-1)
+    int wc;          // steps of the group (its width / T); 0 when the lane has no row
+    bool ok;
+};
+
+// Per-lane group index (several groups per wavefront): vector loads.
+__device__ __forceinline__ GroupMeta group_meta_lane(const SpmvParams &P, int64_t g) {
+    GroupMeta m{0, 0, 0, 0};
+    if (g < P.ng) {
+        if (P.ragged) {
+            m.row0 = P.grp_row0[g];
+            m.sg = P.grp_row0[g + 1] - (int32_t)m.row0;
+        } else {
+            m.row0 = g * P.G;
+            m.sg = (int)min((int64_t)P.G, P.ns - m.row0);
+        }
+        m.g0 = P.gp[g];
+        m.g1 = (P.gend ? P.gend : P.gp + 1)[g];
+    }
+    return m;
+}
+
+template <int T>
+__device__ __forceinline__ LaneRow lane_row_of(const SpmvParams &P, const GroupMeta &m, int lr) {
+    LaneRow L;
+    const int t = lr / T;
+    L.q = lr % T;
+    L.ok = t < m.sg;
+    L.i = m.row0 + t;
+    L.len = L.ok ? P.short_len[L.i] : 0;
+    L.base = L.ok ? m.g0 + (int64_t)t * T + L.q : 0;
+    L.stride = (int64_t)m.sg * T;
+    // slots of a group are fewer than 2^31 (G rows of int32 length)
+    L.wc = L.ok ? (int)((uint32_t)(m.g1 - m.g0) / (uint32_t)L.stride) : 0;
+    return L;
+}
+
+// Row of wave-item w owned by this lane.
+template <int T>
+__device__ __forceinline__ LaneRow lane_row(const SpmvParams &P, int32_t w, int lane) {
+    if (P.wpg > 0) {  // G*T >= 64: wpg wavefronts per group, group index uniform
+        const int32_t g = w / P.wpg;
+        const int lr = (w - g * P.wpg) * 64 + lane;
+        return lane_row_of<T>(P, group_meta_uniform(P, g), lr);
+    }
+    // G*T divides 64: gpw groups per wavefront
+    const int GT = P.G * T;
+    const int64_t g = (int64_t)w * P.gpw + lane / GT;
+    return lane_row_of<T>(P, group_meta_lane(P, g), lane % GT);
+}
+
 template <int K> constexpr int unroll_for() { return K == 1 ? 8 : (K <= 4 ? 4 : (K <= 8 ? 2 : 1)); }
 // Steps in flight per lane of a several-rows-per-lane pass with K right-hand
 // sides: the gathered X rows take about 64 registers (16 steps up to K = 4).
