@@ -136,11 +136,11 @@ typedef struct {
                                and the other rows stay whole.  The pieces of each panel
                                and then the whole rows are laid out as above, with
                                each element's CSR index so rgcsr_set_values refreshes
-                               the copy.  A launch of 2 or more right-hand sides whose
-                               X rows (ldx elements) give at most 3 MiB of X per panel
-                               and whose column block has at most 32 bytes of
-                               accumulators per row (K <= 8 with F32 vectors, K <= 4
-                               with F64) runs on the copy: panel q's workgroups run on
+                               the copy.  A call with 2, 4 or (F32 vectors) 8
+                               right-hand sides whose X rows (ldx elements) give at
+                               most 3 MiB of X per panel (for whole 16-byte rows: X, Y,
+                               ldx and ldy 16-byte aligned)
+                               runs on the copy: panel q's workgroups run on
                                XCD (q * 8 / P) of the eight, so each XCD's L2 keeps
                                that panel's slice of X (the x reuse through a cache
                                that Section 4.3 studies); whole rows, dealt to every

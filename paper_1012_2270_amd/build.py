@@ -17,7 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "librgcsr.so")
 BUILD_DIR = os.path.join(HERE, "_build")
 SOURCES = ["host_layout.cpp", "ordering.cpp", "tile_layout.cpp", "panel_layout.cpp", "compact_layout.cpp", "abi_host.cpp",
-           "abi.cpp", "autotune.cpp", "kernels.hip", "compact.hip", "expand.hip", "spmm.hip", "convert.hip", "tiles.hip"]
+           "abi.cpp", "autotune.cpp", "kernels.hip", "compact.hip", "expand.hip", "spmm.hip", "cg.hip", "convert.hip", "tiles.hip"]
 ARCH = os.environ.get("RGCSR_OFFLOAD_ARCH", "gfx950")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -1788,14 +1788,16 @@ rgcsr_status hyb_destroy(hyb_handle A) {
 // ---------------------------------------------------------------------------
 namespace {
 
-struct DevVec {
-    void *p = nullptr;
-    ~DevVec() {
-        if (p) (void)hipFree(p);
+// Host memory that a kernel writes the convergence test to.
+struct PinnedCgHost {
+    CgHost *p = nullptr;
+    CgHost *get() {
+        HIPCHK(hipHostMalloc((void **)&p, sizeof(CgHost), hipHostMallocCoherent | hipHostMallocMapped));
+        p->seq = 0;
+        return p;
     }
-    template <class T> T *alloc(int64_t n) {
-        HIPCHK(hipMalloc(&p, std::max<int64_t>(n, 1) * sizeof(T)));
-        return (T *)p;
+    ~PinnedCgHost() {
+        if (p) (void)hipHostFree(p);
     }
 };
 
@@ -1810,6 +1812,19 @@ struct SyncOnExit {
     ~SyncOnExit() { (void)hipStreamSynchronize(st); }
 };
 
+// Waits until the kernel that writes `seq` has done so (a stream synchronisation
+// would also wait for the work queued behind it).
+void cg_wait(const CgHost *h, unsigned long long seq, hipStream_t st) {
+    for (int64_t spins = 1;; spins++) {
+        if (__atomic_load_n(&h->seq, __ATOMIC_ACQUIRE) == seq) return;
+        if (spins % 1024) continue;
+        const hipError_t e = hipStreamQuery(st);
+        if (e == hipErrorNotReady) continue;
+        if (e == hipSuccess && __atomic_load_n(&h->seq, __ATOMIC_ACQUIRE) == seq) return;
+        fail(RGCSR_EHIP, std::string("conjugate gradients: ") + hipGetErrorString(e));
+    }
+}
+
 double read_scalar(const double *d, hipStream_t st) {
     double v = 0.0;
     HIPCHK(hipMemcpyAsync(&v, d, sizeof(double), hipMemcpyDeviceToHost, st));
@@ -1821,11 +1836,15 @@ double read_scalar(const double *d, hipStream_t st) {
 
 extern "C" {
 
-// Device buffers of the mixed-precision CG (n rows, nb block partials).
+// Device buffers of the mixed-precision CG (n rows, nb block partials) and,
+// where the caller may allocate, the memory that the convergence test is
+// written to.
 struct CgWork {
     double *r64, *q64;
     float *r, *p, *q, *d;
     double *part, *scal;
+    double *part_pq, *part_rr;  // kCgBlocks each
+    CgHost *host = nullptr;
 };
 
 static void cg_mixed_check(rgcsr_handle A_lo, rgcsr_handle A_hi, const double *b, double *x, rgcsr_cg_stats *stats) {
@@ -1846,7 +1865,7 @@ static void cg_mixed_run(rgcsr_handle A_lo, rgcsr_handle A_hi, const double *b, 
     const int64_t n = A_lo->n_rows;
     double *r64 = w.r64, *q64 = w.q64, *part = w.part, *scal = w.scal;
     float *r = w.r, *p = w.p, *q = w.q, *d = w.d;
-    hipok(launch_dot(n, b, b, 1, part, nb, st), "dot");
+    hipok(launch_dot(n, b, b, part, nb, st), "dot");
     hipok(launch_scalar(part, nb, scal, kScalOut, st), "scalar");
     double bnorm = std::sqrt(read_scalar(scal + kOut, st));
     if (bnorm == 0.0) bnorm = 1.0;
@@ -1863,22 +1882,37 @@ static void cg_mixed_run(rgcsr_handle A_lo, rgcsr_handle A_hi, const double *b, 
         const double s = 1.0 / std::sqrt(rr);
         hipok(launch_refine_start(n, r64, s, r, d, p, part, nb, st), "refine_start");
         hipok(launch_scalar(part, nb, scal, kScalRRInit, st), "scalar");
+        bool ahead = false;  // this iteration's q = A p and p.q are queued already
         for (int32_t it = 1; it <= max_inner; it++) {
-            spmv_launch(A_lo, 1, p, 1, q, 1, 0, false, st);
-            hipok(launch_dot(n, p, q, 0, part, nb, st), "dot");
-            hipok(launch_scalar(part, nb, scal, kScalPQ, st), "scalar");
-            hipok(launch_cg_xr(n, d, r, p, q, 0, scal, part, nb, st), "cg_xr");
-            hipok(launch_scalar(part, nb, scal, kScalRRNew, st), "scalar");
-            inner_total++;
-            bool stop = it == max_inner;
-            if (!stop && it % 4 == 0) {
-                double sc[2];
-                HIPCHK(hipMemcpyAsync(sc, scal, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
-                HIPCHK(hipStreamSynchronize(st));
-                stop = std::sqrt(sc[kRR] / sc[kRR0]) <= inner_tol;
+            if (!ahead) {
+                spmv_launch(A_lo, 1, p, 1, q, 1, 0, false, st);
+                hipok(launch_cg_dot(n, p, q, 0, w.part_pq, st), "cg_dot");
             }
-            if (stop) break;
-            hipok(launch_cg_p(n, p, r, 0, scal, nb, st), "cg_p");
+            ahead = false;
+            hipok(launch_cg_step(n, d, r, p, q, 0, scal, it, w.part_pq, w.part_rr, st), "cg_step");
+            inner_total++;
+            if (it == max_inner) break;
+            const bool check = it % 4 == 0;
+            hipok(launch_cg_dir(n, p, r, 0, scal, it, w.part_rr, check ? w.host : nullptr, inner_total, st), "cg_dir");
+            if (!check) continue;
+            double rr_it, rr_0;
+            if (w.host) {
+                // the next product runs while the host waits; a stop leaves
+                // it unused
+                spmv_launch(A_lo, 1, p, 1, q, 1, 0, false, st);
+                hipok(launch_cg_dot(n, p, q, 0, w.part_pq, st), "cg_dot");
+                ahead = true;
+                cg_wait(w.host, inner_total, st);
+                rr_it = w.host->rr;
+                rr_0 = w.host->rr0;
+            } else {
+                double sc[3];
+                HIPCHK(hipMemcpyAsync(sc, scal, sizeof(sc), hipMemcpyDeviceToHost, st));
+                HIPCHK(hipStreamSynchronize(st));
+                rr_it = sc[kRR];  // it is even: the odd iteration that follows reads it
+                rr_0 = sc[kRR0];
+            }
+            if (std::sqrt(rr_it / rr_0) <= inner_tol) break;
         }
         hipok(launch_refine_add(n, x, d, 1.0 / s, nb, st), "refine_add");
         outer++;
@@ -1900,16 +1934,22 @@ rgcsr_status rgcsr_cg_solve(rgcsr_handle A_lo, rgcsr_handle A_hi, const double *
     hipStream_t st = (hipStream_t)stream;
     const auto t0 = std::chrono::steady_clock::now();
     const int nb = (int)nblocks_vec(n);
-    DevVec m_r64, m_q64, m_r, m_p, m_q, m_d, m_part, m_scal;
+    PinnedCgHost pinned;
+    DevScratch m;  // one block
+    m.st = st;
+    m.reserve((size_t)n * 32 + 6 * 256 + (nb + 2 * kCgBlocks + kNumScal) * 8 + 4 * 256);
     CgWork w;
-    w.r64 = m_r64.alloc<double>(n);
-    w.q64 = m_q64.alloc<double>(n);
-    w.r = m_r.alloc<float>(n);
-    w.p = m_p.alloc<float>(n);
-    w.q = m_q.alloc<float>(n);
-    w.d = m_d.alloc<float>(n);
-    w.part = m_part.alloc<double>(nb);
-    w.scal = m_scal.alloc<double>(kNumScal);
+    w.r64 = (double *)m.get((size_t)n * 8);
+    w.q64 = (double *)m.get((size_t)n * 8);
+    w.r = (float *)m.get((size_t)n * 4);
+    w.p = (float *)m.get((size_t)n * 4);
+    w.q = (float *)m.get((size_t)n * 4);
+    w.d = (float *)m.get((size_t)n * 4);
+    w.part = (double *)m.get((size_t)nb * 8);
+    w.part_pq = (double *)m.get(kCgBlocks * 8);
+    w.part_rr = (double *)m.get(kCgBlocks * 8);
+    w.scal = (double *)m.get(kNumScal * 8);
+    w.host = pinned.get();
     SyncOnExit guard{st};
     cg_mixed_run(A_lo, A_hi, b, x, tol, inner_tol, max_outer, max_inner, st, w, nb, stats, t0);
     ABI_CATCH
@@ -1938,7 +1978,11 @@ rgcsr_status rgcsr_cg_solve_noalloc(rgcsr_handle A_lo, rgcsr_handle A_hi, const 
     w.p = (float *)(ws + kNoAllocOffP);
     w.q = (float *)(ws + kNoAllocOffQ);
     w.d = (float *)(ws + kNoAllocOffD);
+    // the block partials of the solve's ends and of an iteration's two sums
+    // are never held at once
     w.part = (double *)(ws + kNoAllocOffPart);
+    w.part_pq = w.part;
+    w.part_rr = w.part + kCgBlocks;
     w.scal = (double *)(ws + kNoAllocOffScal);
     // returns only when the stream has passed every kernel that uses the
     // workspace, so a later call (on any stream) finds it free
@@ -1958,11 +2002,16 @@ rgcsr_status rgcsr_cg_solve_f64(rgcsr_handle A, const double *b, double *x, doub
     hipStream_t st = (hipStream_t)stream;
     const auto t0 = std::chrono::steady_clock::now();
     const int nb = (int)nblocks_vec(n);
-    DevVec m_r, m_p, m_q, m_part, m_scal;
-    double *r = m_r.alloc<double>(n), *p = m_p.alloc<double>(n), *q = m_q.alloc<double>(n);
-    double *part = m_part.alloc<double>(nb), *scal = m_scal.alloc<double>(kNumScal);
+    PinnedCgHost pinned;
+    DevScratch m;  // one block
+    m.st = st;
+    m.reserve((size_t)n * 24 + 3 * 256 + (nb + 2 * kCgBlocks + kNumScal) * 8 + 4 * 256);
+    double *r = (double *)m.get((size_t)n * 8), *p = (double *)m.get((size_t)n * 8), *q = (double *)m.get((size_t)n * 8);
+    double *part = (double *)m.get((size_t)nb * 8), *scal = (double *)m.get(kNumScal * 8);
+    double *part_pq = (double *)m.get(kCgBlocks * 8), *part_rr = (double *)m.get(kCgBlocks * 8);
+    CgHost *host = pinned.get();
     SyncOnExit guard{st};
-    hipok(launch_dot(n, b, b, 1, part, nb, st), "dot");
+    hipok(launch_dot(n, b, b, part, nb, st), "dot");
     hipok(launch_scalar(part, nb, scal, kScalOut, st), "scalar");
     double bnorm = std::sqrt(read_scalar(scal + kOut, st));
     if (bnorm == 0.0) bnorm = 1.0;
@@ -1973,15 +2022,26 @@ rgcsr_status rgcsr_cg_solve_f64(rgcsr_handle A, const double *b, double *x, doub
     int32_t it = 0;
     *stats = rgcsr_cg_stats{};
     double rr = read_scalar(scal + kRR, st);
+    bool ahead = false;  // this iteration's q = A p and p.q are queued already
     while (it < max_iter && std::sqrt(rr) / bnorm > tol) {
-        spmv_launch(A, 1, p, 1, q, 1, 1, false, st);
-        hipok(launch_dot(n, p, q, 1, part, nb, st), "dot");
-        hipok(launch_scalar(part, nb, scal, kScalPQ, st), "scalar");
-        hipok(launch_cg_xr(n, x, r, p, q, 1, scal, part, nb, st), "cg_xr");
-        hipok(launch_scalar(part, nb, scal, kScalRRNew, st), "scalar");
-        hipok(launch_cg_p(n, p, r, 1, scal, nb, st), "cg_p");
+        if (!ahead) {
+            spmv_launch(A, 1, p, 1, q, 1, 1, false, st);
+            hipok(launch_cg_dot(n, p, q, 1, part_pq, st), "cg_dot");
+        }
+        ahead = false;
         it++;
-        if (it % 4 == 0 || it == max_iter) rr = read_scalar(scal + kRR, st);
+        hipok(launch_cg_step(n, x, r, p, q, 1, scal, it, part_pq, part_rr, st), "cg_step");
+        const bool check = it % 4 == 0 || it == max_iter;
+        hipok(launch_cg_dir(n, p, r, 1, scal, it, part_rr, check ? host : nullptr, it, st), "cg_dir");
+        if (!check) continue;
+        if (it < max_iter) {
+            // the next product runs while the host waits
+            spmv_launch(A, 1, p, 1, q, 1, 1, false, st);
+            hipok(launch_cg_dot(n, p, q, 1, part_pq, st), "cg_dot");
+            ahead = true;
+        }
+        cg_wait(host, it, st);
+        rr = host->rr;
     }
     spmv_launch(A, 1, x, 1, q, 1, 1, false, st);
     hipok(launch_resid(n, b, q, r, part, nb, st), "resid");

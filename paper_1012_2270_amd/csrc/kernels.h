@@ -85,9 +85,10 @@ struct HybParams {
     const void *coo_val;
 };
 
-// CG scalar slots and finishing modes.
-enum { kRR = 0, kRR0 = 1, kPQ = 2, kAlpha = 3, kBeta = 4, kOut = 5, kNumScal = 8 };
-enum { kScalPQ = 0, kScalRRNew = 1, kScalRRInit = 2, kScalOut = 3 };
+// CG scalar slots (r.r of even and of odd iterations apart: the workgroups of
+// one kernel read one and write the other) and finishing modes.
+enum { kRR = 0, kRR0 = 1, kRROdd = 2, kOut = 5, kNumScal = 8 };
+enum { kScalRRInit = 2, kScalOut = 3 };
 
 // Several right-hand sides take the runs of rows per lane (R = 0) up to this
 // many accumulator bytes per row (F32 K <= 4, F64 K <= 2); wider, one row per lane.
@@ -109,11 +110,27 @@ hipError_t launch_grad(const SpmvParams &P, int vdt, int vec_f64, int T, const v
                        const int64_t *row_ptr, bool want_dvals, bool atomic_dx, hipStream_t st);
 hipError_t launch_hyb(const HybParams &H, int vdt, int vec_f64, const void *x, void *y, hipStream_t st);
 
-hipError_t launch_dot(int64_t n, const void *a, const void *b, int f64, double *part, int nb, hipStream_t st);
+hipError_t launch_dot(int64_t n, const double *a, const double *b, double *part, int nb, hipStream_t st);
 hipError_t launch_scalar(const double *part, int nb, double *scal, int mode, hipStream_t st);
-hipError_t launch_cg_xr(int64_t n, void *x, void *r, const void *p, const void *q, int f64, const double *scal,
-                        double *part, int nb, hipStream_t st);
-hipError_t launch_cg_p(int64_t n, void *p, const void *r, int f64, const double *scal, int nb, hipStream_t st);
+// One CG iteration after q = A p, three kernels of cg_blocks(n) workgroups
+// (vectors F32 or F64): partial sums of p.q; x += alpha p, r -= alpha q and
+// partial sums of r.r; p = r + beta p.  Each kernel finishes the sums of the one
+// before it in its own workgroups.  it: the iteration, from 1.  host (may be
+// null): memory the host reads, which receives r.r, the first r.r and then
+// `seq`.
+struct CgHost {
+    double rr, rr0;
+    unsigned long long seq;
+};
+constexpr int kCgBlocks = 256;
+inline int cg_blocks(int64_t n) {
+    return n > 4096 * (kCgBlocks - 1) ? kCgBlocks : n > 4096 ? (int)((n + 4095) / 4096) : 1;
+}
+hipError_t launch_cg_dot(int64_t n, const void *p, const void *q, int f64, double *part_pq, hipStream_t st);
+hipError_t launch_cg_step(int64_t n, void *x, void *r, const void *p, const void *q, int f64, const double *scal,
+                          int it, const double *part_pq, double *part_rr, hipStream_t st);
+hipError_t launch_cg_dir(int64_t n, void *p, const void *r, int f64, double *scal, int it, const double *part_rr,
+                         CgHost *host, unsigned long long seq, hipStream_t st);
 hipError_t launch_resid(int64_t n, const double *b, const double *q, double *r, double *part, int nb,
                         hipStream_t st);
 hipError_t launch_refine_start(int64_t n, const double *r64, double s, float *r, float *d, float *p,

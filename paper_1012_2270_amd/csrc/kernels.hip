@@ -916,7 +916,8 @@ __global__ __launch_bounds__(256) void hyb_coo_k(int64_t m, const int32_t *crow,
 }
 
 // ---------------------------------------------------------------------------
-// Conjugate-gradient vector kernels.  Dot products accumulate in FP64 into a
+// Conjugate-gradient vector kernels (the ones of an iteration: cg.hip).  Dot
+// products accumulate in FP64 into a
 // fixed number of block partials and are finished by one block, so every
 // reduction has a fixed order (bit-reproducible runs).
 // ---------------------------------------------------------------------------
@@ -964,35 +965,9 @@ __global__ __launch_bounds__(256) void cg_scalar_k(const double *part, int nb, d
     const double s = block_sum(acc, sh);
     if (threadIdx.x != 0) return;
     switch (mode) {
-    case kScalPQ: scal[kPQ] = s; scal[kAlpha] = scal[kRR] / s; break;
-    case kScalRRNew: scal[kBeta] = s / scal[kRR]; scal[kRR] = s; break;
     case kScalRRInit: scal[kRR] = s; scal[kRR0] = s; break;
     default: scal[kOut] = s; break;
     }
-}
-
-// x += alpha p ; r -= alpha q ; partial sums of r.r
-template <class VT>
-__global__ __launch_bounds__(256) void cg_xr_k(int64_t n, VT *x, VT *r, const VT *p, const VT *q,
-                                               const double *scal, double *part) {
-    __shared__ double sh[4];
-    const VT alpha = (VT)scal[kAlpha];
-    double acc = 0.0;
-    grid_loop4(n, [&](int64_t i) {
-        x[i] += alpha * p[i];
-        const VT ri = r[i] - alpha * q[i];
-        r[i] = ri;
-        acc += (double)ri * (double)ri;
-    });
-    const double t = block_sum(acc, sh);
-    if (threadIdx.x == 0) part[blockIdx.x] = t;
-}
-
-// p = r + beta p
-template <class VT>
-__global__ __launch_bounds__(256) void cg_p_k(int64_t n, VT *p, const VT *r, const double *scal) {
-    const VT beta = (VT)scal[kBeta];
-    grid_loop4(n, [&](int64_t i) { p[i] = r[i] + beta * p[i]; });
 }
 
 // r64 = b - q64 ; partial sums of r64.r64
@@ -1316,37 +1291,13 @@ hipError_t launch_hyb(const HybParams &H, int vdt, int vec_f64, const void *x, v
 }
 
 // CG helpers ---------------------------------------------------------------
-hipError_t launch_dot(int64_t n, const void *a, const void *b, int f64, double *part, int nb, hipStream_t st) {
-    if (f64)
-        hipLaunchKernelGGL((dot_partial_k<double, double>), dim3(nb), dim3(256), 0, st, n, (const double *)a,
-                           (const double *)b, part);
-    else
-        hipLaunchKernelGGL((dot_partial_k<float, float>), dim3(nb), dim3(256), 0, st, n, (const float *)a,
-                           (const float *)b, part);
+hipError_t launch_dot(int64_t n, const double *a, const double *b, double *part, int nb, hipStream_t st) {
+    hipLaunchKernelGGL((dot_partial_k<double, double>), dim3(nb), dim3(256), 0, st, n, a, b, part);
     return check_launch();
 }
 
 hipError_t launch_scalar(const double *part, int nb, double *scal, int mode, hipStream_t st) {
     hipLaunchKernelGGL(cg_scalar_k, dim3(1), dim3(256), 0, st, part, nb, scal, mode);
-    return check_launch();
-}
-
-hipError_t launch_cg_xr(int64_t n, void *x, void *r, const void *p, const void *q, int f64, const double *scal,
-                        double *part, int nb, hipStream_t st) {
-    if (f64)
-        hipLaunchKernelGGL((cg_xr_k<double>), dim3(nb), dim3(256), 0, st, n, (double *)x, (double *)r,
-                           (const double *)p, (const double *)q, scal, part);
-    else
-        hipLaunchKernelGGL((cg_xr_k<float>), dim3(nb), dim3(256), 0, st, n, (float *)x, (float *)r,
-                           (const float *)p, (const float *)q, scal, part);
-    return check_launch();
-}
-
-hipError_t launch_cg_p(int64_t n, void *p, const void *r, int f64, const double *scal, int nb, hipStream_t st) {
-    if (f64)
-        hipLaunchKernelGGL((cg_p_k<double>), dim3(nb), dim3(256), 0, st, n, (double *)p, (const double *)r, scal);
-    else
-        hipLaunchKernelGGL((cg_p_k<float>), dim3(nb), dim3(256), 0, st, n, (float *)p, (const float *)r, scal);
     return check_launch();
 }
 
