@@ -10,7 +10,6 @@
 #include <cstring>
 #include <rocprim/device/device_radix_sort.hpp>
 #include <rocprim/device/device_scan.hpp>
-#include <rocprim/device/device_select.hpp>
 
 #include "compact.h"
 #include "convert.h"
@@ -132,36 +131,131 @@ __global__ void keys_k(const int64_t *rp, int64_t n, int64_t sigma, int32_t *len
     }
 }
 
-// flags of the long-row split over rows in window order
-__global__ void split_k(const int32_t *ord, const int32_t *len, int64_t n, int64_t tau, uint8_t *is_short,
-                        uint8_t *is_long) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const bool lg = tau >= 0 && len[ord[i]] > tau;
-        is_short[i] = lg ? 0 : 1;
-        is_long[i] = lg ? 1 : 0;
+// Row lengths and the window order of the sort step: a workgroup sorts the rows
+// of one window of up to kWindowSort in LDS, longest first, rows of equal
+// length by index (the index is part of the key, so the order is the stable
+// sort's).  One launch where a radix sort over all rows took 22, each about as
+// long as the work in it (500,009 rows in windows of 512: 230 us, now 15).
+constexpr int kWindowSort = 4096;
+__global__ __launch_bounds__(1024) void window_sort_k(const int64_t *rp, int64_t n, int32_t sigma, int32_t size,
+                                                      int32_t *len, int32_t *ord) {
+    extern __shared__ uint64_t wkey[];  // [size], a power of two of at least the window
+    const int64_t w0 = (int64_t)blockIdx.x * sigma;
+    const int32_t m = (int32_t)std::min<int64_t>(sigma, n - w0);
+    for (int32_t t = threadIdx.x; t < size; t += blockDim.x) {
+        uint64_t k = ~uint64_t(0);
+        if (t < m) {
+            const int32_t l = (int32_t)(rp[w0 + t + 1] - rp[w0 + t]);
+            len[w0 + t] = l;
+            k = (uint64_t)(0x7fffffffu - (uint32_t)l) << 12 | (uint32_t)t;
+        }
+        wkey[t] = k;
+    }
+    __syncthreads();
+    for (int32_t k = 2; k <= size; k *= 2)
+        for (int32_t j = k / 2; j > 0; j /= 2) {
+            for (int32_t t = threadIdx.x; t < size / 2; t += blockDim.x) {
+                const int32_t i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
+                const uint64_t x = wkey[i], y = wkey[i + j];
+                if ((x > y) == ((i & k) == 0)) {
+                    wkey[i] = y;
+                    wkey[i + j] = x;
+                }
+            }
+            __syncthreads();
+        }
+    for (int32_t t = threadIdx.x; t < m; t += blockDim.x) ord[w0 + t] = (int32_t)w0 + (int32_t)(wkey[t] & (kWindowSort - 1));
+}
+
+// Long-row split: the rows in window order go to the grouped rows (at most
+// tau elements) or to the long rows, each in that order.  Counts per tile of
+// kSplitTile rows, their prefix sums (one workgroup), then the lists; three
+// launches where flags, two selections and two gathers of lengths took eleven
+// (500,009 rows: 230 us with the gaps between them, now 33).
+constexpr int kSplitTile = 1024;
+__global__ __launch_bounds__(kSplitTile) void split_count_k(const int32_t *ord, const int32_t *len, int64_t n,
+                                                            int64_t tau, int32_t *cnt) {
+    __shared__ int32_t c;
+    if (threadIdx.x == 0) c = 0;
+    __syncthreads();
+    const int64_t i = (int64_t)blockIdx.x * kSplitTile + threadIdx.x;
+    const uint64_t b = __ballot(i < n && len[ord[i < n ? i : n - 1]] <= tau);
+    if ((threadIdx.x & 63) == 0) atomicAdd(&c, __popcll(b));
+    __syncthreads();
+    if (threadIdx.x == 0) cnt[blockIdx.x] = c;
+}
+
+// cnt becomes its exclusive prefix sum; counts: grouped rows, long rows
+__global__ __launch_bounds__(1024) void split_scan_k(int32_t *cnt, int32_t tiles, int64_t n, int64_t *counts) {
+    __shared__ int32_t sum[16];
+    int32_t before = 0;
+    for (int32_t t0 = 0; t0 < tiles; t0 += 1024) {
+        const int32_t t = t0 + (int)threadIdx.x;
+        const int32_t v = t < tiles ? cnt[t] : 0;
+        int32_t x = v;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t up = __shfl_up(x, off);
+            if ((threadIdx.x & 63) >= off) x += up;
+        }
+        if ((threadIdx.x & 63) == 63) sum[threadIdx.x >> 6] = x;
+        __syncthreads();
+        int32_t total = 0;
+        for (int w = 0; w < 16; w++) {
+            if (w < (int)(threadIdx.x >> 6)) x += sum[w];
+            total += sum[w];
+        }
+        if (t < tiles) cnt[t] = before + x - v;
+        before += total;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        counts[0] = before;
+        counts[1] = n - before;
     }
 }
 
-// lengths of the listed rows; long-list keys (longest first); flags for the
-// plan: bit 0 = some grouped row is out of place, bit 1 = some grouped row is
-// empty
-__global__ void gather_len_k(const int32_t *rows, const int32_t *len, int64_t n, int32_t *out, uint32_t *key,
-                             int32_t *flags) {
+// lens_s, flags: as gather_len_k; key: of the long rows, longest first
+__global__ __launch_bounds__(kSplitTile) void split_write_k(const int32_t *ord, const int32_t *len, int64_t n,
+                                                            int64_t tau, const int32_t *cnt, int32_t *sv,
+                                                            int32_t *lens_s, int32_t *lv, uint32_t *key,
+                                                            int32_t *flags) {
+    __shared__ int32_t sum[kSplitTile / 64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t i0 = (int64_t)blockIdx.x * kSplitTile, i = i0 + threadIdx.x;
+    const int32_t row = ord[i < n ? i : n - 1], l = len[row];
+    const bool is_short = i < n && l <= tau;
+    const uint64_t b = __ballot(is_short);
+    if (lane == 0) sum[wv] = __popcll(b);
+    __syncthreads();
+    int32_t s = cnt[blockIdx.x] + __popcll(b & ((uint64_t(1) << lane) - 1));
+    for (int w = 0; w < kSplitTile / 64; w++) s += w < wv ? sum[w] : 0;
+    int32_t f = 0;
+    if (is_short) {
+        sv[s] = row;
+        lens_s[s] = l;
+        f = (row != s ? 1 : 0) | (l == 0 ? 2 : 0);
+    } else if (i < n) {
+        lv[i - s] = row;
+        key[i - s] = 0x7fffffffu - (uint32_t)l;
+    }
+    f = (__any(f & 1) ? 1 : 0) | (__any(f & 2) ? 2 : 0);
+    if (lane == 0 && f && (__hip_atomic_load(flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & f) != f)
+        atomicOr(flags, f);
+}
+
+// lengths of the grouped rows where none are long; flags for the plan: bit 0 =
+// some grouped row is out of place, bit 1 = some grouped row is empty
+__global__ void gather_len_k(const int32_t *rows, const int32_t *len, int64_t n, int32_t *out, int32_t *flags) {
     int32_t f = 0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         const int32_t l = len[rows[i]];
-        if (out) out[i] = l;
-        if (key) key[i] = 0x7fffffffu - (uint32_t)l;
-        if (flags) {
-            if (rows[i] != i) f |= 1;
-            if (l == 0) f |= 2;
-        }
+        out[i] = l;
+        if (rows[i] != i) f |= 1;
+        if (l == 0) f |= 2;
     }
     // one atomic per wavefront at most: nearly every lane of a permuted layout
     // has a flag to set (47 us before, for 500,009 rows)
-    if (!flags) return;
     f = (__any(f & 1) ? 1 : 0) | (__any(f & 2) ? 2 : 0);
     if ((threadIdx.x & 63) == 0 && f && (__hip_atomic_load(flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & f) != f)
         atomicOr(flags, f);
@@ -307,11 +401,14 @@ void device_plan(DevPlan &P, const LayoutParams &p, int64_t n_rows, int64_t n_co
     // about what the steps below take: row arrays and the groups', the sort
     // keys, the split lists (the long rows' own arrays come on top)
     const bool sorted = p.sigma > 1, split = p.tau >= 0;
-    S.reserve((size_t)n * (18 + (sorted ? 40 : 0) + (split ? 14 : 0)) + (size_t(1) << 17));
-    // one block of what starts at zero: error and layout flags, the pattern
-    // search's state and hash table
+    const int64_t window = std::min(p.sigma, n);
+    const bool in_lds = sorted && window <= kWindowSort;
+    S.reserve((size_t)n * (18 + (sorted && !in_lds ? 40 : 0) + (split ? 14 : 0)) + (size_t(1) << 17));
+    // one block of what starts at zero: error and layout flags, the row counts
+    // of the split, the pattern search's state and hash table
     int32_t *flags = (int32_t *)S.get(64 + kPatHash * sizeof(uint64_t));
     int32_t *pat_state = flags + 4;
+    int64_t *counts = (int64_t *)(flags + 8);
     uint64_t *pat_key = (uint64_t *)(flags + 16);
     CHK(hipMemsetAsync(flags, 0, 64 + (patterns ? kPatHash * sizeof(uint64_t) : 0), st));
     if (validate) {
@@ -319,17 +416,22 @@ void device_plan(DevPlan &P, const LayoutParams &p, int64_t n_rows, int64_t n_co
         hipLaunchKernelGGL(validate_k, dim3(nwg), dim3(kValidateThreads), 0, st, rp, col, n, n_cols, nnz, flags,
                            (unsigned long long *)(flags + 2));
         CHK(hipGetLastError());
-        int32_t ef[4];
-        CHK(hipMemcpyAsync(ef, flags, sizeof(ef), hipMemcpyDeviceToHost, st));
+    }
+    int32_t hf[16];
+    auto read_flags = [&] {
+        CHK(hipMemcpyAsync(hf, flags, sizeof(hf), hipMemcpyDeviceToHost, st));
         CHK(hipStreamSynchronize(st));
-        const int32_t e = ef[0] | (ef[2] || ef[3] ? 8 : 0);
+        if (!validate) return;
+        const int32_t e = hf[0] | (hf[2] || hf[3] ? 8 : 0);
         if (e & 32) fail(RGCSR_EOVERFLOW, "row longer than int32");
         if (e & 1) fail(RGCSR_ECSR, "row_ptr[0] != 0");
         if (e & 2) fail(RGCSR_ECSR, "row_ptr decreases or exceeds nnz");
         if (e & 4) fail(RGCSR_ECSR, "column out of range");
         if (e & 8) fail(RGCSR_ECSR, "columns not strictly ascending");
         if (e & 16) fail(RGCSR_ECSR, "row_ptr[n_rows] != nnz");
-    }
+    };
+    // (the split reads row lengths alone, so its counts come with the errors)
+    if (n == 0 || (validate && !split)) read_flags();
     if (n == 0) {
         P.gp_host.assign(1, 0);
         P.long_ptr_host.assign(1, 0);
@@ -343,10 +445,16 @@ void device_plan(DevPlan &P, const LayoutParams &p, int64_t n_rows, int64_t n_co
     int32_t *len = (int32_t *)S.get(n * 4);
     int32_t *ord = (int32_t *)S.get(n * 4);
     // (one window: the key is the length alone)
-    uint64_t *key = sorted || p.sigma >= n ? (uint64_t *)S.get(n * 8) : nullptr;
+    uint64_t *key = sorted && !in_lds ? (uint64_t *)S.get(n * 8) : nullptr;
     int32_t *row_tmp = key ? (int32_t *)S.get(n * 4) : ord;
-    hipLaunchKernelGGL(keys_k, dim3(nblocks(n)), dim3(256), 0, st, rp, n, std::max<int64_t>(1, p.sigma), len, key,
-                       row_tmp);
+    if (in_lds) {
+        int32_t size = 2;
+        while (size < window) size *= 2;
+        hipLaunchKernelGGL(window_sort_k, dim3((unsigned)((n + window - 1) / window)), dim3(std::clamp(size / 2, 64, 1024)),
+                           size * sizeof(uint64_t), st, rp, n, (int32_t)window, size, len, ord);
+    } else {
+        hipLaunchKernelGGL(keys_k, dim3(nblocks(n)), dim3(256), 0, st, rp, n, p.sigma, len, key, row_tmp);
+    }
     CHK(hipGetLastError());
     if (key) {
         uint64_t *key_out = (uint64_t *)S.get(n * 8);
@@ -358,33 +466,35 @@ void device_plan(DevPlan &P, const LayoutParams &p, int64_t n_rows, int64_t n_co
             return rocprim::radix_sort_pairs(t, b, key, key_out, row_tmp, ord, (size_t)n, 0u, end_bit, st);
         });
     }
-    // long-row split, both lists in window order
+    // long-row split, both lists in window order; lengths, order and emptiness
+    // flags of the grouped rows
     int32_t *sv = ord, *lv0 = nullptr;
+    uint32_t *lk = nullptr;
+    int32_t *lens_s = (int32_t *)S.get(n * 4);
     P.ns = n;
     P.nl = 0;
     if (split) {
-        uint8_t *fs = (uint8_t *)S.get(n), *fl = (uint8_t *)S.get(n);
-        hipLaunchKernelGGL(split_k, dim3(nblocks(n)), dim3(256), 0, st, ord, len, n, p.tau, fs, fl);
-        CHK(hipGetLastError());
+        const int32_t tiles = (int32_t)((n + kSplitTile - 1) / kSplitTile);
+        int32_t *cnt = (int32_t *)S.get((size_t)tiles * 4);
         sv = (int32_t *)S.get(n * 4);
         lv0 = (int32_t *)S.get(n * 4);
-        size_t *counts = (size_t *)S.get(2 * sizeof(size_t));
-        with_temp(S, [&](void *t, size_t &b) { return rocprim::select(t, b, ord, fs, sv, counts, (size_t)n, st); });
-        with_temp(S, [&](void *t, size_t &b) { return rocprim::select(t, b, ord, fl, lv0, counts + 1, (size_t)n, st); });
-        size_t hc[2];
-        CHK(hipMemcpyAsync(hc, counts, sizeof(hc), hipMemcpyDeviceToHost, st));
-        CHK(hipStreamSynchronize(st));
-        P.ns = (int64_t)hc[0];
-        P.nl = (int64_t)hc[1];
-    }
-    const int64_t ns = P.ns, nl = P.nl;
-    // grouped rows: lengths, order and emptiness flags, group widths, offsets
-    int32_t *lens_s = (int32_t *)S.get(std::max<int64_t>(1, ns) * 4);
-    if (ns) {
-        hipLaunchKernelGGL(gather_len_k, dim3(std::min(nblocks(ns), 512)), dim3(256), 0, st, sv, len, ns, lens_s, (uint32_t *)nullptr,
-                           flags + 1);
+        lk = (uint32_t *)S.get(n * 4);
+        hipLaunchKernelGGL(split_count_k, dim3(tiles), dim3(kSplitTile), 0, st, ord, len, n, p.tau, cnt);
+        hipLaunchKernelGGL(split_scan_k, dim3(1), dim3(1024), 0, st, cnt, tiles, n, counts);
+        hipLaunchKernelGGL(split_write_k, dim3(tiles), dim3(kSplitTile), 0, st, ord, len, n, p.tau, cnt, sv, lens_s, lv0,
+                           lk, flags + 1);
+        CHK(hipGetLastError());
+        read_flags();
+        int64_t hc[2];
+        memcpy(hc, hf + 8, sizeof(hc));
+        P.ns = hc[0];
+        P.nl = hc[1];
+    } else {
+        hipLaunchKernelGGL(gather_len_k, dim3(std::min(nblocks(n), 512)), dim3(256), 0, st, sv, len, n, lens_s, flags + 1);
         CHK(hipGetLastError());
     }
+    const int64_t ns = P.ns, nl = P.nl;
+    // group widths, offsets
     P.ng = (ns + p.G - 1) / p.G;
     int64_t *gp = (int64_t *)S.get((P.ng + 1) * 8);
     CHK(hipMemsetAsync(gp, 0, 8, st));
@@ -401,10 +511,7 @@ void device_plan(DevPlan &P, const LayoutParams &p, int64_t n_rows, int64_t n_co
     int64_t *lp = (int64_t *)S.get((nl + 1) * 8);
     CHK(hipMemsetAsync(lp, 0, 8, st));
     if (nl) {
-        uint32_t *lk = (uint32_t *)S.get(nl * 4), *lk2 = (uint32_t *)S.get(nl * 4);
-        hipLaunchKernelGGL(gather_len_k, dim3(nblocks(nl)), dim3(256), 0, st, lv0, len, nl, (int32_t *)nullptr, lk,
-                           (int32_t *)nullptr);
-        CHK(hipGetLastError());
+        uint32_t *lk2 = (uint32_t *)S.get(nl * 4);
         lv = (int32_t *)S.get(nl * 4);
         with_temp(S, [&](void *t, size_t &b) {
             return rocprim::radix_sort_pairs(t, b, lk, lk2, lv0, lv, (size_t)nl, 0u, 31u, st);
@@ -432,11 +539,10 @@ void device_plan(DevPlan &P, const LayoutParams &p, int64_t n_rows, int64_t n_co
     if (nl) CHK(hipMemcpyAsync(P.long_ptr_host.data(), lp, (nl + 1) * 8, hipMemcpyDeviceToHost, st));
     CHK(hipMemcpyAsync(small, flags, sizeof(small), hipMemcpyDeviceToHost, st));
     CHK(hipStreamSynchronize(st));
-    const int32_t hf = small[1];
     P.slots = P.gp_host[P.ng];
     P.long_nnz = P.long_ptr_host[nl];
-    P.perm = (hf & 1) != 0;
-    P.no_empty = (hf & 2) == 0;
+    P.perm = (small[1] & 1) != 0;
+    P.no_empty = (small[1] & 2) == 0;
     P.sv = sv;
     P.lv = lv;
     P.lens_s = lens_s;

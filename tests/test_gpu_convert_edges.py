@@ -74,3 +74,20 @@ def test_long_rows_in_pieces(torch_cuda, lens):
     for dt in ("f32", "bf16"):
         same_handles(on_device(torch_cuda, A, G=64, sigma=512, tau=16, value_dtype=dt),
                      rg.rgcsr_from_csr(A, G=64, sigma=512, tau=16, value_dtype=dt))
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1023, 1024, 1025, 4095, 4096, 4097, 9001, 1024 * 1025 + 7])
+@pytest.mark.parametrize("sigma", [1, 2, 3, 512, 4095, 4096, 4097, 1 << 40])
+def test_window_order_and_split(torch_cuda, n, sigma):
+    """Many rows of equal length (the order within a length is the rows' own),
+    windows on both sides of the largest that is sorted in LDS, and tiles of
+    the split that hold only short rows, only long ones and none."""
+    rng = np.random.default_rng(n)
+    lens = rng.integers(0, 5, n)
+    lens[n // 3:n // 2] = 4
+    cols = np.arange(lens.sum()) - np.repeat(np.concatenate([[0], np.cumsum(lens)[:-1]]), lens)
+    A = W.CSR(n, 7, np.concatenate([[0], np.cumsum(lens)]).astype(np.int64), cols.astype(np.int32),
+              np.arange(1, len(cols) + 1, dtype=np.float32))
+    say("converter windows", n, sigma)
+    for tau in (-1, 0, 2, 4):
+        same_handles(on_device(torch_cuda, A, G=64, sigma=sigma, tau=tau), rg.rgcsr_from_csr(A, G=64, sigma=sigma, tau=tau))
