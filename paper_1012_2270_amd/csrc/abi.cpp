@@ -954,7 +954,7 @@ bool narrow_launch_ok(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx
 }
 
 void spmv_launch(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx, void *Y, int64_t ldy, int f64,
-                 bool persistent, hipStream_t st) {
+                 bool persistent, hipStream_t st, double *dot_part = nullptr) {
     if (h->n_rows == 0) return;
     const bool panels = panel_launch_ok(h, K, X, ldx, Y, ldy, f64);
     const rgcsr_matrix_s *pn = h->PN;
@@ -1053,6 +1053,7 @@ void spmv_launch(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx, voi
     }
     if (h->compact != kCompactNone && K == 1) {
         P.n_wave_items = (int32_t)((h->ng * h->wpg + h->compact_rows - 1) / h->compact_rows);
+        P.dot_part = dot_part;
         e = launch_spmv_compact(P, vd, f64, h->compact_rows, h->compact_width, st);
     } else {
         e = launch_spmv(P, vd, f64, h->prm.T, K, R, K == 1 ? h->lp : 0, (int)nwg, st);
@@ -1064,6 +1065,19 @@ void spmv_launch(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx, voi
                            nullptr, 0, f64, K, st);
         if (e != hipSuccess) fail(RGCSR_EHIP, std::string("combine launch: ") + hipGetErrorString(e));
     }
+}
+
+// Parts of x.y that an SpMV over h leaves in dot_part: those of the row
+// patterns' workgroups, or 0 where a kernel of its own has to do it.  Every
+// workgroup of the next kernel adds them all, so their number is bounded (a
+// kernel of its own reads the two vectors: at 2M rows 16 MB, 4 us, and the
+// parts of 256 workgroups 16 MB from the L2s).
+constexpr int kDotParts = 8192;
+int spmv_dot_parts(const rgcsr_matrix_s *h) {
+    if (h->compact != kCompactPattern) return 0;
+    const int64_t waves = (h->ng * h->wpg + h->compact_rows - 1) / h->compact_rows;
+    const int64_t n = (waves + kBlockWaves - 1) / kBlockWaves;
+    return n <= kDotParts && n <= h->n_rows ? (int)n : 0;
 }
 
 // CG vector kernels: up to 2,048 workgroups (eight per CU), each lane taking
@@ -1844,6 +1858,7 @@ struct CgWork {
     float *r, *p, *q, *d;
     double *part, *scal;
     double *part_pq, *part_rr;  // kCgBlocks each
+    double *part_spmv;          // kDotParts, or n (fewer parts than rows)
     CgHost *host = nullptr;
 };
 
@@ -1865,6 +1880,13 @@ static void cg_mixed_run(rgcsr_handle A_lo, rgcsr_handle A_hi, const double *b, 
     const int64_t n = A_lo->n_rows;
     double *r64 = w.r64, *q64 = w.q64, *part = w.part, *scal = w.scal;
     float *r = w.r, *p = w.p, *q = w.q, *d = w.d;
+    const int in_spmv = spmv_dot_parts(A_lo);
+    const int n_pq = in_spmv ? in_spmv : cg_blocks(n);
+    double *part_pq = in_spmv ? w.part_spmv : w.part_pq;
+    auto product = [&] {  // q = A p and the parts of p.q
+        spmv_launch(A_lo, 1, p, 1, q, 1, 0, false, st, in_spmv ? part_pq : nullptr);
+        if (!in_spmv) hipok(launch_cg_dot(n, p, q, 0, part_pq, st), "cg_dot");
+    };
     hipok(launch_dot(n, b, b, part, nb, st), "dot");
     hipok(launch_scalar(part, nb, scal, kScalOut, st), "scalar");
     double bnorm = std::sqrt(read_scalar(scal + kOut, st));
@@ -1884,12 +1906,9 @@ static void cg_mixed_run(rgcsr_handle A_lo, rgcsr_handle A_hi, const double *b, 
         hipok(launch_scalar(part, nb, scal, kScalRRInit, st), "scalar");
         bool ahead = false;  // this iteration's q = A p and p.q are queued already
         for (int32_t it = 1; it <= max_inner; it++) {
-            if (!ahead) {
-                spmv_launch(A_lo, 1, p, 1, q, 1, 0, false, st);
-                hipok(launch_cg_dot(n, p, q, 0, w.part_pq, st), "cg_dot");
-            }
+            if (!ahead) product();
             ahead = false;
-            hipok(launch_cg_step(n, d, r, p, q, 0, scal, it, w.part_pq, w.part_rr, st), "cg_step");
+            hipok(launch_cg_step(n, d, r, p, q, 0, scal, it, part_pq, n_pq, w.part_rr, st), "cg_step");
             inner_total++;
             if (it == max_inner) break;
             const bool check = it % 4 == 0;
@@ -1899,8 +1918,7 @@ static void cg_mixed_run(rgcsr_handle A_lo, rgcsr_handle A_hi, const double *b, 
             if (w.host) {
                 // the next product runs while the host waits; a stop leaves
                 // it unused
-                spmv_launch(A_lo, 1, p, 1, q, 1, 0, false, st);
-                hipok(launch_cg_dot(n, p, q, 0, w.part_pq, st), "cg_dot");
+                product();
                 ahead = true;
                 cg_wait(w.host, inner_total, st);
                 rr_it = w.host->rr;
@@ -1949,6 +1967,7 @@ rgcsr_status rgcsr_cg_solve(rgcsr_handle A_lo, rgcsr_handle A_hi, const double *
     w.part_pq = (double *)m.get(kCgBlocks * 8);
     w.part_rr = (double *)m.get(kCgBlocks * 8);
     w.scal = (double *)m.get(kNumScal * 8);
+    w.part_spmv = w.q64;  // the FP64 product is not in use between the residuals
     w.host = pinned.get();
     SyncOnExit guard{st};
     cg_mixed_run(A_lo, A_hi, b, x, tol, inner_tol, max_outer, max_inner, st, w, nb, stats, t0);
@@ -1983,6 +2002,7 @@ rgcsr_status rgcsr_cg_solve_noalloc(rgcsr_handle A_lo, rgcsr_handle A_hi, const 
     w.part = (double *)(ws + kNoAllocOffPart);
     w.part_pq = w.part;
     w.part_rr = w.part + kCgBlocks;
+    w.part_spmv = w.q64;
     w.scal = (double *)(ws + kNoAllocOffScal);
     // returns only when the stream has passed every kernel that uses the
     // workspace, so a later call (on any stream) finds it free
@@ -2002,14 +2022,20 @@ rgcsr_status rgcsr_cg_solve_f64(rgcsr_handle A, const double *b, double *x, doub
     hipStream_t st = (hipStream_t)stream;
     const auto t0 = std::chrono::steady_clock::now();
     const int nb = (int)nblocks_vec(n);
+    const int in_spmv = spmv_dot_parts(A);
+    const int n_pq = in_spmv ? in_spmv : cg_blocks(n);
     PinnedCgHost pinned;
     DevScratch m;  // one block
     m.st = st;
-    m.reserve((size_t)n * 24 + 3 * 256 + (nb + 2 * kCgBlocks + kNumScal) * 8 + 4 * 256);
+    m.reserve((size_t)n * 24 + 3 * 256 + (nb + n_pq + kCgBlocks + kNumScal) * 8 + 4 * 256);
     double *r = (double *)m.get((size_t)n * 8), *p = (double *)m.get((size_t)n * 8), *q = (double *)m.get((size_t)n * 8);
     double *part = (double *)m.get((size_t)nb * 8), *scal = (double *)m.get(kNumScal * 8);
-    double *part_pq = (double *)m.get(kCgBlocks * 8), *part_rr = (double *)m.get(kCgBlocks * 8);
+    double *part_pq = (double *)m.get((size_t)n_pq * 8), *part_rr = (double *)m.get(kCgBlocks * 8);
     CgHost *host = pinned.get();
+    auto product = [&] {  // q = A p and the parts of p.q
+        spmv_launch(A, 1, p, 1, q, 1, 1, false, st, in_spmv ? part_pq : nullptr);
+        if (!in_spmv) hipok(launch_cg_dot(n, p, q, 1, part_pq, st), "cg_dot");
+    };
     SyncOnExit guard{st};
     hipok(launch_dot(n, b, b, part, nb, st), "dot");
     hipok(launch_scalar(part, nb, scal, kScalOut, st), "scalar");
@@ -2024,20 +2050,16 @@ rgcsr_status rgcsr_cg_solve_f64(rgcsr_handle A, const double *b, double *x, doub
     double rr = read_scalar(scal + kRR, st);
     bool ahead = false;  // this iteration's q = A p and p.q are queued already
     while (it < max_iter && std::sqrt(rr) / bnorm > tol) {
-        if (!ahead) {
-            spmv_launch(A, 1, p, 1, q, 1, 1, false, st);
-            hipok(launch_cg_dot(n, p, q, 1, part_pq, st), "cg_dot");
-        }
+        if (!ahead) product();
         ahead = false;
         it++;
-        hipok(launch_cg_step(n, x, r, p, q, 1, scal, it, part_pq, part_rr, st), "cg_step");
+        hipok(launch_cg_step(n, x, r, p, q, 1, scal, it, part_pq, n_pq, part_rr, st), "cg_step");
         const bool check = it % 4 == 0 || it == max_iter;
         hipok(launch_cg_dir(n, p, r, 1, scal, it, part_rr, check ? host : nullptr, it, st), "cg_dir");
         if (!check) continue;
         if (it < max_iter) {
             // the next product runs while the host waits
-            spmv_launch(A, 1, p, 1, q, 1, 1, false, st);
-            hipok(launch_cg_dot(n, p, q, 1, part_pq, st), "cg_dot");
+            product();
             ahead = true;
         }
         cg_wait(host, it, st);

@@ -2,15 +2,16 @@
 //
 // A short solve is bound by launches and by the waits between them, a long one
 // by the vectors' bytes.  One workgroup of 1,024 threads per CU reads 16 bytes
-// per load; each kernel first adds the partial sums of the one before it (at
-// most 256, one per thread, in a fixed order, the same in every workgroup), so
-// no kernel of one workgroup stands between them: three launches an iteration
-// beside the SpMV instead of five.  27-point 96^3 (884,736 rows), BF16, 136
-// iterations: these kernels 20.7 us an iteration before and 13.7 now (3.5 MB to
-// 17.7 MB each, held by the Infinity Cache: bound by launch and by the wait for
-// the first loads), the gap every fourth iteration, where the host decides,
-// filled by the next product; the solve 6.85 -> 4.88 ms.  Sums are FP64 and in
-// a fixed order, so a solve gives the same bits every time.
+// per load; each kernel first adds the partial sums of the one before it (in a
+// fixed order, the same in every workgroup), so no kernel of one workgroup
+// stands between them: three launches an iteration beside the SpMV instead of
+// five, two where the SpMV leaves the parts of p.q.  27-point 96^3 (884,736
+// rows), BF16, 136 iterations: 20.7 us an iteration before, 13.7 as three
+// kernels (3.5 to 17.7 MB each, held by the Infinity Cache: bound by launch and
+// by the wait for the first loads), 10.9 and 0.9 more in the SpMV as two; the
+// gap every fourth iteration, where the host decides, is filled by the next
+// product; the solve 6.85 -> 4.64 ms.  Sums are FP64 and in a fixed order, so a
+// solve gives the same bits every time.
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"
@@ -33,8 +34,10 @@ __device__ __forceinline__ double cg_block_sum(double v) {
     return t;
 }
 
-__device__ __forceinline__ double cg_finish(const double *part) {
-    return cg_block_sum(threadIdx.x < gridDim.x ? part[threadIdx.x] : 0.0);
+__device__ __forceinline__ double cg_finish(const double *part, int n) {
+    double v = 0.0;
+    for (int i = threadIdx.x; i < n; i += kCgThreads) v += part[i];
+    return cg_block_sum(v);
 }
 
 // 16 bytes of a vector that starts at any element
@@ -84,11 +87,12 @@ __global__ __launch_bounds__(kCgThreads) void cg_dot_k(int64_t n, const VT *p, c
 
 template <class VT>
 __global__ __launch_bounds__(kCgThreads) void cg_step_k(int64_t n, VT *x, VT *r, const VT *p, const VT *q,
-                                                        const double *rr, const double *part_pq, double *part_rr) {
+                                                        const double *rr, const double *part_pq, int n_pq,
+                                                        double *part_rr) {
     using VV = typename CgVec<VT>::type;
     using VA = typename CgVec<VT>::at;
     constexpr int W = CgVec<VT>::W;
-    const VT alpha = (VT)(*rr / cg_finish(part_pq));
+    const VT alpha = (VT)(*rr / cg_finish(part_pq, n_pq));
     double acc = 0.0;
     auto one = [&](int64_t i, VV xv, VV rv, const VV &pv, const VV &qv) {
 #pragma unroll
@@ -130,7 +134,7 @@ __global__ __launch_bounds__(kCgThreads) void cg_dir_k(int64_t n, VT *p, const V
     using VV = typename CgVec<VT>::type;
     using VA = typename CgVec<VT>::at;
     constexpr int W = CgVec<VT>::W;
-    const double s = cg_finish(part_rr);
+    const double s = cg_finish(part_rr, (int)gridDim.x);
     const VT beta = (VT)(s / *rr_old);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         *rr_new = s;
@@ -171,15 +175,15 @@ hipError_t launch_cg_dot(int64_t n, const void *p, const void *q, int f64, doubl
 static int rr_slot(int it) { return it % 2 ? kRR : kRROdd; }
 
 hipError_t launch_cg_step(int64_t n, void *x, void *r, const void *p, const void *q, int f64, const double *scal,
-                          int it, const double *part_pq, double *part_rr, hipStream_t st) {
+                          int it, const double *part_pq, int n_pq, double *part_rr, hipStream_t st) {
     const dim3 g(cg_blocks(n)), b(kCgThreads);
     const double *rr = scal + rr_slot(it);
     if (f64)
         hipLaunchKernelGGL(cg_step_k<double>, g, b, 0, st, n, (double *)x, (double *)r, (const double *)p,
-                           (const double *)q, rr, part_pq, part_rr);
+                           (const double *)q, rr, part_pq, n_pq, part_rr);
     else
         hipLaunchKernelGGL(cg_step_k<float>, g, b, 0, st, n, (float *)x, (float *)r, (const float *)p,
-                           (const float *)q, rr, part_pq, part_rr);
+                           (const float *)q, rr, part_pq, n_pq, part_rr);
     return hipGetLastError();
 }
 

@@ -68,6 +68,7 @@ struct SpmvParams {
     int32_t last_col;              // n_cols - 1
     const uint8_t *pat_id;         // [ns]
     const int32_t *pat_tab;        // [pat_ints]
+    double *dot_part;              // [workgroups] parts of x.y (row patterns), or null
     const uint16_t *col16;         // [slots]
     const int32_t *win;            // [2 * units]
     // vectors
@@ -127,8 +128,9 @@ inline int cg_blocks(int64_t n) {
     return n > 4096 * (kCgBlocks - 1) ? kCgBlocks : n > 4096 ? (int)((n + 4095) / 4096) : 1;
 }
 hipError_t launch_cg_dot(int64_t n, const void *p, const void *q, int f64, double *part_pq, hipStream_t st);
+// (n_pq parts of p.q: cg_blocks(n), or those that the SpMV left)
 hipError_t launch_cg_step(int64_t n, void *x, void *r, const void *p, const void *q, int f64, const double *scal,
-                          int it, const double *part_pq, double *part_rr, hipStream_t st);
+                          int it, const double *part_pq, int n_pq, double *part_rr, hipStream_t st);
 hipError_t launch_cg_dir(int64_t n, void *p, const void *r, int f64, double *scal, int it, const double *part_rr,
                          CgHost *host, unsigned long long seq, hipStream_t st);
 hipError_t launch_resid(int64_t n, const double *b, const double *q, double *r, double *part, int nb,

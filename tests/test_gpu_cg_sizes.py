@@ -69,3 +69,25 @@ def test_cg_sizes(torch_cuda, oracle, n):
     assert all(t == runs[0] for t in runs)   # the same bits every time, with either workspace
     assert rg.rgcsr_cg_solve(lo, M, bd, torch.zeros(n, dtype=torch.float64, device="cuda:0"), max_outer=1,
                              max_inner=5)["inner_iterations"] == 5
+
+
+@pytest.mark.parametrize("n", [61, 4097, 40001])
+@pytest.mark.parametrize("G", [64, 128, 32])
+def test_cg_product_and_its_sum(torch_cuda, oracle, n, G):
+    """p.q from the SpMV (row patterns: whole wavefronts of rows) and from a
+    kernel of its own (G = 32): the same solution, iterations within one check
+    of the oracle's."""
+    torch = torch_cuda
+    A = tridiagonal(n)
+    b = oracle.csr_spmv(A, W.uniform_vector(n, 8))
+    M = rg.rgcsr_from_csr(A, value_dtype="f64", G=G)
+    lo = rg.rgcsr_from_csr(A, value_dtype="f32", G=G)
+    _, it_orc, _ = oracle.cg(A, b, tol=1e-10)
+    say("cg sum", n, G)
+    for solve in (lambda x: rg.rgcsr_cg_solve_f64(M, dev(b), x, tol=1e-10), lambda x: rg.rgcsr_cg_solve(lo, M, dev(b), x)):
+        xd = torch.zeros(n, dtype=torch.float64, device="cuda:0")
+        st = solve(xd)
+        r = b - oracle.csr_spmv(A, host(xd))
+        assert math.sqrt(float(np.dot(r, r)) / float(np.dot(b, b))) <= 1.01e-10
+        if st["outer_iterations"] == 0:
+            assert abs(st["inner_iterations"] - it_orc) <= 4
