@@ -143,6 +143,7 @@ struct rgcsr_matrix_s {
     std::shared_ptr<HostExpand> pending_expand;  // until the runs are built
     // compact columns of the grouped rows (compact.h)
     int32_t compact = kCompactNone, compact_rows = 1, compact_width = 0, n_pat = 0, pat_stride = 0;
+    PatSegs segs;
     uint8_t *pat_id = nullptr;
     int32_t *pat_tab = nullptr, *win = nullptr;
     uint16_t *col16 = nullptr;
@@ -344,6 +345,7 @@ template <class C> void add_compact_arrays(rgcsr_matrix_s *h, const C &c, Arena 
     if (c.mode == kCompactPattern) {
         h->n_pat = c.n_pat;
         h->pat_stride = c.stride;
+        h->segs = c.segs;
         a.add(&h->pat_id, (size_t)h->ns);
         a.add(&h->pat_tab, (size_t)c.n_pat * c.stride);
     } else if (c.mode == kCompactWindow) {
@@ -1054,7 +1056,8 @@ void spmv_launch(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx, voi
     if (h->compact != kCompactNone && K == 1) {
         P.n_wave_items = (int32_t)((h->ng * h->wpg + h->compact_rows - 1) / h->compact_rows);
         P.dot_part = dot_part;
-        e = launch_spmv_compact(P, vd, f64, h->compact_rows, h->compact_width, st);
+        const bool segs = h->segs.n && !h->perm && !h->ragged && h->compact_rows == 1;
+        e = launch_spmv_compact(P, vd, f64, h->compact_rows, h->compact_width, segs ? &h->segs : nullptr, st);
     } else {
         e = launch_spmv(P, vd, f64, h->prm.T, K, R, K == 1 ? h->lp : 0, (int)nwg, st);
     }

@@ -61,6 +61,20 @@ constexpr bool pat_pays(int64_t n_pat, int64_t stride, int64_t slots) {
 // the values take 4 bytes or less.
 constexpr int compact_rows(int64_t width, int esz) { return width <= 8 && esz < 8 ? 2 : 1; }
 
+// The x entries that a workgroup's rows (kBlockThreads consecutive ones, one
+// lane per row) need under the row patterns: for each of n runs of nearby
+// offsets, x at its first row + lo and the kBlockThreads + span - 1 entries
+// behind it.  The workgroup copies them to LDS, the run's first at `base`, so
+// a row's step reads LDS where it would gather.
+constexpr int kPatSegs = 9;
+struct PatSegs {
+    int32_t n = 0;      // 0: not used; entries behind n repeat the last
+    int32_t extra = 0;  // sum of the spans
+    int32_t total = 0;  // entries in LDS
+    int32_t lo[kPatSegs] = {}, span[kPatSegs] = {}, base[kPatSegs] = {};
+};
+PatSegs pattern_segments(const int32_t *tab, int32_t n_pat, int32_t stride);
+
 struct HostCompact {
     int mode = kCompactNone;
     int32_t rows = 1;              // rows per lane
@@ -68,6 +82,7 @@ struct HostCompact {
     int32_t n_pat = 0, stride = 0;
     std::vector<uint8_t> pat_id;   // [ns] pattern of each grouped row
     std::vector<int32_t> pat_tab;  // [n_pat * stride] length, offsets
+    PatSegs segs;
     std::vector<int32_t> win;      // [2 * units] first column and column count of each unit's window
     std::vector<uint16_t> col16;   // [slots] column - first column of the unit (0 in padding of empty rows)
 };
@@ -98,8 +113,9 @@ hipError_t launch_col16(const int64_t *gp, int64_t ng, int32_t unit_groups, int6
 
 // SpMV of one right-hand side over the compact form (P.compact):
 // P.n_wave_items wavefronts of `rows` groups each, four to a workgroup.
-// width: the widest group (patterns).
+// width: the widest group (patterns).  segs: of the patterns, when every
+// workgroup's rows are consecutive; null otherwise.
 hipError_t launch_spmv_compact(const SpmvParams &P, int vdt, int vec_f64, int32_t rows, int32_t width,
-                               hipStream_t st);
+                               const PatSegs *segs, hipStream_t st);
 
 }  // namespace rg

@@ -21,7 +21,7 @@ namespace rg {
 //
 // Bound by the value stream (patterns: 7-point 128^3 FP32 77 MB instead of
 // 134, 23.5 -> 14.4 us, 5.4 TB/s; 27-point 101^3 FP64 238 MB instead of 344,
-// 64.5 -> 48.0 us) and, where the columns are random in a band, by the x
+// 64.5 -> 40.7 us) and, where the columns are random in a band, by the x
 // gathers: one touches about 28 cache lines, so gathering from LDS counts for
 // more than the two bytes saved (400,009 rows of 24 nonzeros, half band 500,
 // BF16: 20.0 -> 11.4 us; with the 16-bit columns alone 18.9).
@@ -87,6 +87,19 @@ template <int VD, int R, int U, bool WIN, bool LEN> struct CompactRows {
             }
     }
 };
+
+// The workgroup's part of x.y
+__device__ __forceinline__ void put_dot(const SpmvParams &P, double d) {
+    __shared__ double part[kBlockWaves];
+    for (int off = 32; off > 0; off >>= 1) d += __shfl_xor(d, off);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = d;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = part[0];
+        for (int i = 1; i < kBlockWaves; i++) t += part[i];
+        P.dot_part[blockIdx.x] = t;
+    }
+}
 
 // Row patterns.  Steps past a row's length read on in the table (the entries
 // behind it are another row's, or none) and gather at the clamped column they
@@ -159,19 +172,93 @@ __global__ __launch_bounds__(kBlockThreads) void spmv_pattern_k(SpmvParams P) {
     for (int r = 0; r < R; r++)
         if (G.ok[r]) ((A *)P.y)[(int64_t)G.orow[r] * P.ldy] = acc[r];
     if constexpr (DOT) {
-        __shared__ double part[kBlockWaves];
         double d = 0.0;
 #pragma unroll
         for (int r = 0; r < R; r++) d += G.ok[r] ? (double)xd[r] * (double)acc[r] : 0.0;
-        for (int off = 32; off > 0; off >>= 1) d += __shfl_xor(d, off);
-        if (lane == 0) part[threadIdx.x >> 6] = d;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double t = part[0];
-            for (int i = 1; i < kBlockWaves; i++) t += part[i];
-            P.dot_part[blockIdx.x] = t;
+        put_dot(P, d);
+    }
+}
+
+// Row patterns whose x comes from LDS (PatSegs): 27 steps issue 27 value loads
+// and 10 of x instead of 27 gathers, all before anything waits (27-point 101^3,
+// FP64: 48.0 -> 40.7 us, 5.8 TB/s).  NS: the runs, a constant, as a count read from
+// memory made each run's load wait for a scalar load of its own (FP32 96^3:
+// 24.8 us); further ones repeat the last.
+template <int VD, class A, int U, int NS, bool DOT>
+__global__ __launch_bounds__(kBlockThreads) void spmv_segment_k(SpmvParams P, PatSegs Q) {
+    using V = Val<VD>;
+    __shared__ int32_t tab[kPatTab + 32];
+    extern __shared__ __align__(16) char seg_lds[];
+    A *xs = (A *)seg_lds;  // [Q.total]
+    const int tid = threadIdx.x, lane = tid & 63;
+    int32_t tv[kPatTab / kBlockThreads];
+#pragma unroll
+    for (int i = 0; i < kPatTab / kBlockThreads; i++) {
+        const int32_t e = tid + i * kBlockThreads;
+        if (i * kBlockThreads < P.pat_ints) tv[i] = P.pat_tab[e < P.pat_ints ? e : 0];
+    }
+    const int32_t unit = xcd_remap(blockIdx.x, gridDim.x);
+    const int32_t row0 = unit * kBlockThreads;
+    const A *X = (const A *)P.x;
+    auto at = [&](int64_t c) { return X[min(max(c, (int64_t)0), (int64_t)P.last_col) * P.ldx]; };
+    A xr[NS];
+#pragma unroll
+    for (int s = 0; s < NS; s++) xr[s] = at((int64_t)row0 + Q.lo[s] + tid);
+    // the entries behind each run's first kBlockThreads, one lane each
+    int32_t eo = 0, ed = 0;
+    {
+        int32_t before = 0;
+#pragma unroll
+        for (int s = 0; s < NS; s++) {
+                if (tid >= before) {
+                    eo = Q.lo[s] + kBlockThreads + tid - before;
+                    ed = Q.base[s] + kBlockThreads + tid - before;
+                }
+                before += Q.span[s];
+            }
+    }
+    const A xe = at((int64_t)row0 + eo);
+    const int32_t w = __builtin_amdgcn_readfirstlane(unit * kBlockWaves + (tid >> 6));
+    CompactRows<VD, 1, U, false, false> G;
+    G.meta(P, w, lane);
+    int32_t pt = P.pat_id[G.rowi[0]];
+    A xd = A(0);
+    if constexpr (DOT) xd = X[(int64_t)G.orow[0] * P.ldx];
+    G.load(0);
+#pragma unroll
+    for (int s = 0; s < NS; s++) xs[Q.base[s] + tid] = xr[s];
+    if (tid < Q.extra) xs[ed] = xe;
+    // offsets become places in xs (of the workgroup's first row); the lengths
+    // before each list stay
+#pragma unroll
+    for (int i = 0; i < kPatTab / kBlockThreads; i++) {
+        const int32_t e = tid + i * kBlockThreads;
+        if (i * kBlockThreads < P.pat_ints) {
+            int32_t place = 0;
+#pragma unroll
+            for (int s = 0; s < NS; s++)
+                if (tv[i] >= Q.lo[s]) place = tv[i] - Q.lo[s] + Q.base[s];
+            if (e < P.pat_ints) tab[e] = e % P.pat_stride ? place : tv[i];
         }
     }
+    __syncthreads();
+    pt *= P.pat_stride;
+    const int32_t len = G.ok[0] ? tab[pt] : 0;
+    A acc = A(0);
+    for (int c0 = 0; c0 < G.cmax; c0 += U) {
+        if (c0) G.load(c0);
+        A xv[U];
+#pragma unroll
+        for (int u = 0; u < U; u++)
+            xv[u] = xs[min((uint32_t)(tid + tab[pt + 1 + c0 + u]), (uint32_t)(Q.total - 1))];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const A f = fmaA(V::template cvt<A>(G.v[0][u]), xv[u], acc);
+            acc = c0 + u < len ? f : acc;
+        }
+    }
+    if (G.ok[0]) ((A *)P.y)[(int64_t)G.orow[0] * P.ldy] = acc;
+    if constexpr (DOT) put_dot(P, G.ok[0] ? (double)xd * (double)acc : 0.0);
 }
 
 // x windows, one right-hand side of unit stride or not.  LEN: row lengths are
@@ -260,8 +347,27 @@ static int pattern_steps(int32_t width, std::initializer_list<int> counts) {
     return best;
 }
 
+template <int VD, class A, int NS, bool DOT>
+static hipError_t launch_segment_v(const SpmvParams &P, int32_t width, int nwg, const PatSegs &segs, hipStream_t st) {
+    const dim3 g(nwg), b(kBlockThreads);
+    const size_t lds = segs.total * sizeof(A);
+    if (pattern_steps(width, {9, 27}) == 9)
+        hipLaunchKernelGGL((spmv_segment_k<VD, A, 9, NS, DOT>), g, b, lds, st, P, segs);
+    else
+        hipLaunchKernelGGL((spmv_segment_k<VD, A, 27, NS, DOT>), g, b, lds, st, P, segs);
+    return hipGetLastError();
+}
+
 template <int VD, class A, bool DOT>
-static hipError_t launch_pattern_v(const SpmvParams &P, int32_t rows, int32_t width, int nwg, hipStream_t st) {
+static hipError_t launch_pattern_v(const SpmvParams &P, int32_t rows, int32_t width, int nwg, const PatSegs *segs,
+                                   hipStream_t st) {
+    // 16-bit values gather: what they save on bytes the longer way to the first
+    // step costs (27-point 96^3: BF16 16.1 us gathered, 18.6 from LDS; FP32 19.5
+    // and 19.0; FP64 41.9 and 36.3)
+    if constexpr (VD == RGCSR_F64 || VD == RGCSR_F32) {
+        if (segs && segs->n <= 3) return launch_segment_v<VD, A, 3, DOT>(P, width, nwg, *segs, st);
+        if (segs) return launch_segment_v<VD, A, kPatSegs, DOT>(P, width, nwg, *segs, st);
+    }
     if (rows == 2) {
         switch (pattern_steps(width, {4, 5, 7, 8})) {
         case 4: RG_GO(spmv_pattern_k<VD, A, 2, 4, DOT>);
@@ -280,7 +386,8 @@ static hipError_t launch_pattern_v(const SpmvParams &P, int32_t rows, int32_t wi
 }
 
 template <int VD, class A>
-static hipError_t launch_compact_v(const SpmvParams &P, int32_t rows, int32_t width, hipStream_t st) {
+static hipError_t launch_compact_v(const SpmvParams &P, int32_t rows, int32_t width, const PatSegs *segs,
+                                   hipStream_t st) {
     const int nwg = (P.n_wave_items + kBlockWaves - 1) / kBlockWaves;
     if (P.compact == kCompactWindow) {
         // 8-byte values: half the steps (22.1 against 23.0 us on 9.6M nonzeros)
@@ -293,21 +400,21 @@ static hipError_t launch_compact_v(const SpmvParams &P, int32_t rows, int32_t wi
         if (len) RG_GO(spmv_window_k<VD, A, 1, U, true>);
         RG_GO(spmv_window_k<VD, A, 1, U, false>);
     }
-    if (P.dot_part) return launch_pattern_v<VD, A, true>(P, rows, width, nwg, st);
-    return launch_pattern_v<VD, A, false>(P, rows, width, nwg, st);
+    if (P.dot_part) return launch_pattern_v<VD, A, true>(P, rows, width, nwg, segs, st);
+    return launch_pattern_v<VD, A, false>(P, rows, width, nwg, segs, st);
 }
 
 hipError_t launch_spmv_compact(const SpmvParams &P, int vdt, int vec_f64, int32_t rows, int32_t width,
-                               hipStream_t st) {
+                               const PatSegs *segs, hipStream_t st) {
     if (vec_f64) {
-        if (vdt == RGCSR_F64) return launch_compact_v<RGCSR_F64, double>(P, rows, width, st);
-        if (vdt == RGCSR_F32) return launch_compact_v<RGCSR_F32, double>(P, rows, width, st);
+        if (vdt == RGCSR_F64) return launch_compact_v<RGCSR_F64, double>(P, rows, width, segs, st);
+        if (vdt == RGCSR_F32) return launch_compact_v<RGCSR_F32, double>(P, rows, width, segs, st);
         return hipErrorInvalidValue;
     }
     switch (vdt) {
-    case RGCSR_F32: return launch_compact_v<RGCSR_F32, float>(P, rows, width, st);
-    case RGCSR_F16: return launch_compact_v<RGCSR_F16, float>(P, rows, width, st);
-    case RGCSR_BF16: return launch_compact_v<RGCSR_BF16, float>(P, rows, width, st);
+    case RGCSR_F32: return launch_compact_v<RGCSR_F32, float>(P, rows, width, segs, st);
+    case RGCSR_F16: return launch_compact_v<RGCSR_F16, float>(P, rows, width, segs, st);
+    case RGCSR_BF16: return launch_compact_v<RGCSR_BF16, float>(P, rows, width, segs, st);
     }
     return hipErrorInvalidValue;
 }

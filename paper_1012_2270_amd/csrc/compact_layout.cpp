@@ -72,8 +72,46 @@ bool find_patterns(const HostLayout &L, HostCompact &C) {
         t[0] = (int32_t)lists[p].size();
         std::copy(lists[p].begin(), lists[p].end(), t + 1);
     }
+    C.segs = pattern_segments(C.pat_tab.data(), C.n_pat, C.stride);
     return true;
 }
+
+}  // namespace
+
+// Runs of offsets with gaps of at most 64, where the runs' loads are at most
+// half the gathers they replace (27 points in three dimensions: 9 runs and one
+// load of the runs' ends; 7 points: 5 runs, not worth it).
+PatSegs pattern_segments(const int32_t *tab, int32_t n_pat, int32_t stride) {
+    std::vector<int32_t> off;
+    int32_t longest = 0;
+    for (int32_t p = 0; p < n_pat; p++) {
+        const int32_t *t = tab + (size_t)p * stride;
+        longest = std::max(longest, t[0]);
+        off.insert(off.end(), t + 1, t + 1 + t[0]);
+    }
+    std::sort(off.begin(), off.end());
+    PatSegs S;
+    for (size_t i = 0; i < off.size(); i++) {
+        if (i == 0 || (int64_t)off[i] - off[i - 1] > 64) {
+            if (S.n == kPatSegs) return PatSegs();
+            S.lo[S.n++] = off[i];
+        }
+        S.span[S.n - 1] = off[i] - S.lo[S.n - 1];
+    }
+    for (int32_t s = 0; s < S.n; s++) {
+        S.base[s] = S.total;
+        S.total += kBlockThreads + S.span[s];
+        S.extra += S.span[s];
+    }
+    for (int32_t s = S.n; s > 0 && s < kPatSegs; s++) {
+        S.lo[s] = S.lo[s - 1];
+        S.base[s] = S.base[s - 1];
+    }
+    if (2 * (S.n + 1) > longest || S.extra > kBlockThreads || S.total > kWinCols) return PatSegs();
+    return S;
+}
+
+namespace {
 
 // x windows of the layout's units; false when some unit's columns span more
 // than kWinCols or the windows do not pay.

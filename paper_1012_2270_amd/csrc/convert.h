@@ -8,6 +8,7 @@
 #include <cstdint>
 #include <vector>
 
+#include "compact.h"
 #include "internal.h"
 
 namespace rg {
@@ -45,6 +46,7 @@ struct DevPlan {
     int32_t n_pat = 0, pat_stride = 0;  // n_pat = 0: none
     const uint8_t *pat_id = nullptr;    // [n_rows] in CSR row order
     const int32_t *pat_tab = nullptr;   // [n_pat * pat_stride]
+    std::vector<int32_t> pat_host;      // its copy, when n_pat > 0
     DevScratch scratch;
 };
 
@@ -70,6 +72,7 @@ struct DevCompact {
     int32_t rows = 1, width = 0, n_pat = 0, stride = 0;  // as HostCompact
     int64_t units = 0;
     const int32_t *win = nullptr;  // [2 * units]
+    PatSegs segs;
 };
 DevCompact device_compact(DevPlan &P, const LayoutParams &p, int esz, const int64_t *rp, const int32_t *col,
                           hipStream_t st);

@@ -535,6 +535,10 @@ void device_plan(DevPlan &P, const LayoutParams &p, int64_t n_rows, int64_t n_co
     P.gp_host.resize(P.ng + 1);
     P.long_ptr_host.assign(nl + 1, 0);
     int32_t small[8];
+    if (patterns) {
+        P.pat_host.resize(kPatTab);
+        CHK(hipMemcpyAsync(P.pat_host.data(), P.pat_tab, kPatTab * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    }
     CHK(hipMemcpyAsync(P.gp_host.data(), gp, (P.ng + 1) * 8, hipMemcpyDeviceToHost, st));
     if (nl) CHK(hipMemcpyAsync(P.long_ptr_host.data(), lp, (nl + 1) * 8, hipMemcpyDeviceToHost, st));
     CHK(hipMemcpyAsync(small, flags, sizeof(small), hipMemcpyDeviceToHost, st));
@@ -622,6 +626,7 @@ DevCompact device_compact(DevPlan &P, const LayoutParams &p, int esz, const int6
         C.mode = kCompactPattern;
         C.n_pat = P.n_pat;
         C.stride = P.pat_stride;
+        C.segs = pattern_segments(P.pat_host.data(), C.n_pat, C.stride);
         C.width = C.stride - 1;
         C.rows = compact_rows(C.width, esz);
         return C;
