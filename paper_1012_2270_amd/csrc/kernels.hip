@@ -16,7 +16,7 @@
 //   hyb_coo_k      adds the remaining entries per row run.
 //   setval_k,      value update and backward pass over the same walk.
 //   grad_k
-//   dot/axpy       conjugate-gradient vector kernels (FP64 dot accumulation).
+//   dot/refine     conjugate-gradient vector kernels (FP64 dot accumulation).
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -916,10 +916,10 @@ __global__ __launch_bounds__(256) void hyb_coo_k(int64_t m, const int32_t *crow,
 }
 
 // ---------------------------------------------------------------------------
-// Conjugate-gradient vector kernels (the ones of an iteration: cg.hip).  Dot
-// products accumulate in FP64 into a
-// fixed number of block partials and are finished by one block, so every
-// reduction has a fixed order (bit-reproducible runs).
+// Conjugate-gradient vector kernels of a solve's start and end (those of an
+// iteration: cg.hip).  Dot products accumulate in FP64 into a fixed number of
+// block partials and are finished by one block, so every reduction has a fixed
+// order (bit-reproducible runs).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ double block_sum(double v, double *sh) {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
