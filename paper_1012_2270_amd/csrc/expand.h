@@ -84,7 +84,7 @@ struct ExpandWave {
 
 // Everything the two kernels read.  Device pointers.
 struct ExpandParams {
-    SpmvParams P;             // layout, x, y; unit stride
+    SpmvParams P;             // layout, x (unit stride), y (any)
     const ExpandPart *parts;  // [n_parts]
     const uint16_t *lcol;     // [entries] column within the tile, tile order
     const int32_t *dst;       // [runs] the run's place in unit order

@@ -174,7 +174,7 @@ __device__ __forceinline__ void run_multiply(const SpmvParams &P, int32_t first,
                 acc = c0 + u < h.len[r] ? f : acc;
             }
         }
-        if (h.len[r] >= 0) ((A *)P.y)[h.row[r]] = acc;
+        if (h.len[r] >= 0) ((A *)P.y)[(int64_t)h.row[r] * P.ldy] = acc;
     }
 }
 
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(kBlockThreads) void expand_spmv_k(ExpandParams E) {
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1)
             if (off < TL) acc += __shfl_xor(acc, off);
-        if (ok && q == 0) ((A *)P.y)[orow] = acc;
+        if (ok && q == 0) ((A *)P.y)[(int64_t)orow * P.ldy] = acc;
         return;
     }
     // block item: a chunk of one row, unit after unit; sums of one unit, then
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(kBlockThreads) void expand_spmv_k(ExpandParams E) {
     if (threadIdx.x == 0) {
         tot = A(0);
         for (int i = 0; i < kBlockWaves; i++) tot += red[i];
-        if (it.c == 1) ((A *)P.y)[ldc(P.long_row, (int64_t)it.a)] = tot;
+        if (it.c == 1) ((A *)P.y)[(int64_t)ldc(P.long_row, (int64_t)it.a) * P.ldy] = tot;
         else ((A *)P.partial)[(int64_t)it.d + it.b] = tot;
     }
 }
