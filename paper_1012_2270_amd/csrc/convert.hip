@@ -136,18 +136,23 @@ __global__ void keys_k(const int64_t *rp, int64_t n, int64_t sigma, int32_t *len
 // length by index (the index is part of the key, so the order is the stable
 // sort's).  One launch where a radix sort over all rows took 22, each about as
 // long as the work in it (500,009 rows in windows of 512: 230 us, now 15).
+//
+// Windows of up to half of kWindowRows share a workgroup (the window leads the
+// key), so a launch never has more threads than rows: a workgroup per window
+// would pass the 2^32 threads of a grid at 2^27 rows in windows of two.
 constexpr int kWindowSort = 4096;
-__global__ __launch_bounds__(1024) void window_sort_k(const int64_t *rp, int64_t n, int32_t sigma, int32_t size,
-                                                      int32_t *len, int32_t *ord) {
-    extern __shared__ uint64_t wkey[];  // [size], a power of two of at least the window
-    const int64_t w0 = (int64_t)blockIdx.x * sigma;
-    const int32_t m = (int32_t)std::min<int64_t>(sigma, n - w0);
+constexpr int kWindowRows = 128;
+__global__ __launch_bounds__(1024) void window_sort_k(const int64_t *rp, int64_t n, int32_t sigma, int32_t rows,
+                                                      int32_t size, int32_t *len, int32_t *ord) {
+    extern __shared__ uint64_t wkey[];  // [size], a power of two of at least `rows`, whole windows
+    const int64_t w0 = (int64_t)blockIdx.x * rows;
+    const int32_t m = (int32_t)std::min<int64_t>(rows, n - w0);
     for (int32_t t = threadIdx.x; t < size; t += blockDim.x) {
         uint64_t k = ~uint64_t(0);
         if (t < m) {
             const int32_t l = (int32_t)(rp[w0 + t + 1] - rp[w0 + t]);
             len[w0 + t] = l;
-            k = (uint64_t)(0x7fffffffu - (uint32_t)l) << 12 | (uint32_t)t;
+            k = (uint64_t)(uint32_t)(t / sigma) << 44 | (uint64_t)(0x7fffffffu - (uint32_t)l) << 12 | (uint32_t)t;
         }
         wkey[t] = k;
     }
@@ -448,10 +453,11 @@ void device_plan(DevPlan &P, const LayoutParams &p, int64_t n_rows, int64_t n_co
     uint64_t *key = sorted && !in_lds ? (uint64_t *)S.get(n * 8) : nullptr;
     int32_t *row_tmp = key ? (int32_t *)S.get(n * 4) : ord;
     if (in_lds) {
+        const int64_t rows = std::max<int64_t>(1, kWindowRows / window) * window;
         int32_t size = 2;
-        while (size < window) size *= 2;
-        hipLaunchKernelGGL(window_sort_k, dim3((unsigned)((n + window - 1) / window)), dim3(std::clamp(size / 2, 64, 1024)),
-                           size * sizeof(uint64_t), st, rp, n, (int32_t)window, size, len, ord);
+        while (size < rows) size *= 2;
+        hipLaunchKernelGGL(window_sort_k, dim3((unsigned)((n + rows - 1) / rows)), dim3(std::clamp(size / 2, 64, 1024)),
+                           size * sizeof(uint64_t), st, rp, n, (int32_t)window, (int32_t)rows, size, len, ord);
     } else {
         hipLaunchKernelGGL(keys_k, dim3(nblocks(n)), dim3(256), 0, st, rp, n, p.sigma, len, key, row_tmp);
     }
