@@ -54,16 +54,33 @@ def _code_of_tensor(t) -> int:
     return _tensor_codes[t.dtype]
 
 
-def _stream(stream=None) -> int:
-    """Handle of the stream, or of the current device's current one: read
+def _raw_current_stream():
+    """A function that reads the handle of the current device's current stream
     without a torch.cuda.Stream object around it, which costs 3.3 us of the 9
-    that a small SpMV call took (its launch: 4)."""
+    that a small SpMV call took (its launch: 4); through the public object in a
+    torch build without these two functions."""
+    torch = _torch()
+    handle = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    device = getattr(torch._C, "_cuda_getDevice", None)
+    if handle is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: handle(device())
+
+
+_current_stream = None
+
+
+def _stream(stream=None) -> int:
+    """Handle of the stream, or of the current device's current one."""
+    global _current_stream
     if stream is not None:
         return stream.cuda_stream
     torch = _torch()
-    if torch.cuda.is_initialized():
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-    return torch.cuda.current_stream().cuda_stream
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    if _current_stream is None:
+        _current_stream = _raw_current_stream()
+    return _current_stream()
 
 
 def _astream(A, stream=None) -> int:
