@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kBlockThreads) void spmv_pattern_k(SpmvParams P) {
 
 // Row patterns whose x comes from LDS (PatSegs): 27 steps issue 27 value loads
 // and 10 of x instead of 27 gathers, all before anything waits (27-point 101^3,
-// FP64: 48.0 -> 40.7 us, 5.8 TB/s).  NS: the runs, a constant, as a count read from
+// FP64: 48.0 -> 40.7 us, 5.8 TB/s).  Where they pay: runs_pay below.  NS: the runs, a constant, as a count read from
 // memory made each run's load wait for a scalar load of its own (FP32 96^3:
 // 24.8 us); further ones repeat the last.
 template <int VD, class A, int U, int NS, bool DOT>
@@ -358,16 +358,30 @@ static hipError_t launch_segment_v(const SpmvParams &P, int32_t width, int nwg, 
     return hipGetLastError();
 }
 
+// x from LDS runs pays for 8-byte vectors of rows wide enough against the loads
+// of the kernel that is compiled (3 or 9 runs, and their ends).  400,000 rows
+// on diagonals in k runs of w, one handle repeated, gathered against runs.  FP64:
+//   1 x 6   6.0, 6.6 us    3 x 3   7.4,  6.9    1 x 17  13.7, 11.2    3 x 9  19.9, 15.6
+//   4 x 4  12.1, 12.8      5 x 3  12.2, 12.2    6 x 3   13.7, 13.1    9 x 3  20.1, 17.2
+// FP32 values with FP64 vectors:
+//   3 x 5   7.9, 8.5       1 x 17  9.3, 8.7     3 x 9   13.1, 10.6    9 x 3  13.1, 13.2
+// FP32 vectors gather, with 16-bit values too: what the runs save on requests
+// the longer way to the first step costs (9 x 3 9.0, 11.5; 3 x 9 8.7, 8.9; 4 x 3
+// 5.0, 9.1; 27-point 96^3 in BF16 16.1, 18.6).
+static bool runs_pay(int vd, int32_t runs, int32_t width) {
+    if (vd == RGCSR_F64) return width >= (runs <= 3 ? 8 : 18);
+    return runs <= 3 && width >= 16;
+}
+
 template <int VD, class A, bool DOT>
 static hipError_t launch_pattern_v(const SpmvParams &P, int32_t rows, int32_t width, int nwg, const PatSegs *segs,
                                    hipStream_t st) {
-    // 16-bit values gather: what they save on bytes the longer way to the first
-    // step costs (27-point 96^3: BF16 16.1 us gathered, 18.6 from LDS; FP32 19.5
-    // and 19.0; FP64 41.9 and 36.3)
-    if constexpr (VD == RGCSR_F64 || VD == RGCSR_F32) {
-        if (segs && segs->n <= 3) return launch_segment_v<VD, A, 3, DOT>(P, width, nwg, *segs, st);
-        if (segs) return launch_segment_v<VD, A, kPatSegs, DOT>(P, width, nwg, *segs, st);
-    }
+    if constexpr (sizeof(A) == 8)
+        if (segs && runs_pay(VD, segs->n, width)) {
+            if (segs->n <= 3) return launch_segment_v<VD, A, 3, DOT>(P, width, nwg, *segs, st);
+            if constexpr (VD == RGCSR_F64)
+                return launch_segment_v<VD, A, kPatSegs, DOT>(P, width, nwg, *segs, st);
+        }
     if (rows == 2) {
         switch (pattern_steps(width, {4, 5, 7, 8})) {
         case 4: RG_GO(spmv_pattern_k<VD, A, 2, 4, DOT>);

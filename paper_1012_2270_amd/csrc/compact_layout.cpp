@@ -78,15 +78,12 @@ bool find_patterns(const HostLayout &L, HostCompact &C) {
 
 }  // namespace
 
-// Runs of offsets with gaps of at most 64, where the runs' loads are at most
-// half the gathers they replace (27 points in three dimensions: 9 runs and one
-// load of the runs' ends; 7 points: 5 runs, not worth it).
+// Runs of offsets with gaps of at most 64; none where they are more than
+// kPatSegs, or their entries do not fit one load of the ends and the buffer.
 PatSegs pattern_segments(const int32_t *tab, int32_t n_pat, int32_t stride) {
     std::vector<int32_t> off;
-    int32_t longest = 0;
     for (int32_t p = 0; p < n_pat; p++) {
         const int32_t *t = tab + (size_t)p * stride;
-        longest = std::max(longest, t[0]);
         off.insert(off.end(), t + 1, t + 1 + t[0]);
     }
     std::sort(off.begin(), off.end());
@@ -107,7 +104,7 @@ PatSegs pattern_segments(const int32_t *tab, int32_t n_pat, int32_t stride) {
         S.lo[s] = S.lo[s - 1];
         S.base[s] = S.base[s - 1];
     }
-    if (2 * (S.n + 1) > longest || S.extra > kBlockThreads || S.total > kWinCols) return PatSegs();
+    if (S.n == 0 || S.extra > kBlockThreads || S.total > kWinCols) return PatSegs();
     return S;
 }
 
