@@ -35,8 +35,12 @@ constexpr int kExpandUnitBytes = 60 << 10;  // LDS of a unit (a launch may take 
 constexpr int kExpandMinRun = 12;        // mean entries of a (tile, unit) pair; below it the padding to
                                          // whole runs costs as much as the entries (FP64, 6.5M nonzeros
                                          // at 22 a pair: 60.1 against 64.2 us with column tiles)
-constexpr int64_t kExpandMinNnz64 = 800000;  // FP64 storage: fewer nonzeros stay with the column tiles
-                                         // (620,000: 15.1 against 14.2 us, 980,000: 16.4 against 17.5)
+// FP64 storage: fewer nonzeros stay with the column tiles, whose x a handle
+// multiplied again and again finds in the L2 (Zipf rows, two steps against tiles,
+// one handle repeated and three in turn: 1.35M nonzeros 20.3 and 18.1 against 16.2
+// and 18.9 us, 2.0M 23.5 and 20.6 against 20.2 and 22.3, 2.3M 24.3 and 21.9
+// against 24.4 and 26.0).
+constexpr int64_t kExpandMinNnz64 = 2200000;
 constexpr int expand_cols(int f64) { return kExpandBytes / (f64 ? 8 : 4); }
 
 // Unit of the multiply step: slots [begin, begin + n) of the grouped part (row

@@ -25,8 +25,8 @@ def test_strided_y(lay, vt, ldy):
     # of two chunks, whose sums a kernel of their own adds
     # (FP64 takes the two steps at larger sizes)
     big = vt == "f64"
-    A = skewed(60_037 if big else 40_037, 1_100_001 if big else 50_001, 1,
-               LONGS * (2 if big else 1) + [16_384 + 4096 + 5], empty=0.03)
+    A = skewed(200_037 if big else 40_037, 400_001 if big else 50_001, 1,
+               LONGS * (4 if big else 1) + [16_384 + 4096 + 5], empty=0.03)
     M = rg.rgcsr_from_csr(A, value_dtype=vt, **lay)
     # the same rows in column tiles take other memory: M does not hold tiles
     T = rg.rgcsr_from_csr(A, value_dtype=vt, tile_min_len=256, **lay)
