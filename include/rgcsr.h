@@ -323,8 +323,9 @@ rgcsr_status rgcsr_spmv(rgcsr_handle A, const void *x, void *y, rgcsr_dtype vec_
  * (device pointers, elements of vec_dtype).  For a batch handle this is
  * Y_m = A_m X_m for every matrix m.  Any k up to 32 runs as one launch, X and
  * Y at any element alignment and with any ldx and ldy; more columns run as
- * launches of equal width.  (A second small launch adds chunk partial sums of
- * rows over 16,384 nonzeros.)
+ * launches of 32 columns and one of the rest (31 and 2 where 33 are left).
+ * (A second small launch adds chunk partial sums of rows over 16,384
+ * nonzeros.)
  * Handles with lanes_per_row > 1 or F16/BF16 stored values run one
  * single-column launch per column.  persistent = 1 launches a fixed grid of
  * wavefronts that loop over the work items (one resident launch); 0 launches

@@ -1374,12 +1374,14 @@ rgcsr_status rgcsr_spmv_batched(rgcsr_handle A, int32_t k, const void *X, int64_
         const int32_t left = k - done;
         int32_t kb = 1;
         if (blocks) {
-            // one launch, or as few of equal width as kSpmmMax columns each
-            // allow (a panel copy serves widths of its own kernels only: three
+            // one launch, or launches of kSpmmMax columns and one of the rest:
+            // the widest kernel has no idle lanes (40 columns as 32 and 8 or as
+            // 20 and 20: Zipf 10^6 FP32 440 and 488 us, FP64 719 and 980;
+            // 27-point 50^3 FP32 62 and 73).  (A panel copy serves widths of its own kernels only: three
             // columns in two launches on it take 170 us, in one on the layout
-            // 125; twelve 216 and 172)
-            const int32_t n = (left + kSpmmMax - 1) / kSpmmMax;
-            kb = (left + n - 1) / n;
+            // 125; twelve 216 and 172.)  No column is left alone: a launch of
+            // one refuses X of 4 GiB and more.
+            kb = left == kSpmmMax + 1 ? kSpmmMax - 1 : std::min(left, kSpmmMax);
         }
         spmv_launch(A, kb, xp, ldx, yp, ldy, f64, persistent != 0, (hipStream_t)stream);
         done += kb;
