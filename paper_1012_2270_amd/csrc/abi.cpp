@@ -951,8 +951,14 @@ bool panel_launch_ok(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx,
 // which it reads in one load, unless row patterns give the columns (Zipf 10^6,
 // k = 2 and 4: 80.6 and 106.8 us against 111 and 124 with lanes sharing rows;
 // 27-point 80^3 with patterns: 25.4 and 28.1 against 19.5 and 21.9).
+// Four FP64 columns stay with it as well where no row is long and there are few
+// row groups or much padding (rows of 4 nonzeros in a band as they come, one
+// lane a row against lanes sharing rows: 30,000 rows 4.7 and 5.9 us, 200,000 12.7
+// and 13.2; rows of 20: 30,000 10.4 and 10.7, but 300,000 49.8 and 47.1).
 bool narrow_launch_ok(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx, const void *Y, int64_t ldy, int f64) {
-    return lane_kernel_ok(K, X, ldx, Y, ldy, f64) && K * (f64 ? 8 : 4) <= kRunsRowBytes && h->compact != kCompactPattern;
+    if (!lane_kernel_ok(K, X, ldx, Y, ldy, f64) || h->compact == kCompactPattern) return false;
+    return K * (f64 ? 8 : 4) <= kRunsRowBytes ||
+           (f64 && K == 4 && h->nl == 0 && (h->ns < kSpmmBusyWaves * 64 || 4 * h->slots >= 7 * h->nnz));
 }
 
 void spmv_launch(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx, void *Y, int64_t ldy, int f64,
@@ -1015,7 +1021,7 @@ void spmv_launch(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx, voi
         return;
     }
     if (K > 1 && !narrow) {
-        e = launch_spmm(P, vd, f64, K, (int)nwg, st);
+        e = launch_spmm(P, SpmmFill{h->ns, h->slots, h->nnz - h->long_nnz}, vd, f64, K, (int)nwg, st);
         if (e == hipSuccess) e = launch_spmm_combine(h->combine, (int32_t)h->n_combine, h->long_row, h->partial, Y, ldy, f64, K, st);
         if (e != hipSuccess) fail(RGCSR_EHIP, std::string("spmm launch: ") + hipGetErrorString(e));
         return;

@@ -57,8 +57,10 @@ __device__ __forceinline__ void spmm_fma(A a, const typename VecOf<A, VW>::type 
     }
 }
 
-// 64 rows of the grouped part (a wave item).
-template <int VD, class A, int VW, int KL, bool PAT>
+// 64 rows of the grouped part (a wave item).  MASK: X rows are loaded up to a
+// row's own length only (spmm_masked); otherwise steps past it load again, with
+// no branch around a load.
+template <int VD, class A, int VW, int KL, bool PAT, bool MASK>
 __device__ __forceinline__ void spmm_groups(const SpmvParams &P, const SpmmCols<A, VW> &C, int32_t w, int lane,
                                             const int32_t *tab) {
     using V = Val<VD>;
@@ -107,7 +109,8 @@ __device__ __forceinline__ void spmm_groups(const SpmvParams &P, const SpmmCols<
                 int32_t c;
                 if constexpr (PAT) c = (int32_t)min((uint32_t)(rowb[b] + tab[ptb[b] + c0 + u]), (uint32_t)P.last_col);
                 else c = KL == 1 ? ci[u] : __shfl(ci[u], src);
-                xv[u][b] = *reinterpret_cast<const XA *>(C.x + (int64_t)c * C.ldx);
+                if constexpr (MASK) xv[u][b] = X(A(0));
+                if (!MASK || c0 + u < lenb[b]) xv[u][b] = *reinterpret_cast<const XA *>(C.x + (int64_t)c * C.ldx);
             }
 #pragma unroll
         for (int u = 0; u < U; u++)
@@ -207,7 +210,7 @@ __device__ __forceinline__ void spmm_block_item(const SpmvParams &P, const SpmmC
     __syncthreads();
 }
 
-template <int VD, class A, int VW, int KL, bool LONG, bool PAT>
+template <int VD, class A, int VW, int KL, bool LONG, bool PAT, bool MASK>
 __global__ __launch_bounds__(kBlockThreads) void spmm_k(SpmvParams P, int32_t k) {
     using X = typename VecOf<A, VW>::type;
     __shared__ X red[LONG ? kBlockWaves : 1][KL];
@@ -229,45 +232,65 @@ __global__ __launch_bounds__(kBlockThreads) void spmm_k(SpmvParams P, int32_t k)
         const int32_t w = __builtin_amdgcn_readfirstlane((u - (LONG ? P.n_block_items : 0)) * kBlockWaves + wv);
         if (w >= P.n_wave_items) continue;
         if (LONG && w < P.n_wave_long) spmm_wave_long<VD, A, VW, KL>(P, C, w, lane);
-        else spmm_groups<VD, A, VW, KL, PAT>(P, C, w - (LONG ? P.n_wave_long : 0), lane, tab);
+        else spmm_groups<VD, A, VW, KL, PAT, MASK>(P, C, w - (LONG ? P.n_wave_long : 0), lane, tab);
     }
 }
 
+// Whether X rows past a row's length are left out.  It pays where the loads are
+// what bounds the launch, from about eight wavefronts of row groups per CU, four
+// with long rows beside them, and while the steps walked are 3/2 of the nonzeros
+// or more (twice with one step in flight).  Loaded again against left out:
+// 300,000 rows of 4 nonzeros in a band, rows as they come (2.8 and 2.5 steps a
+// nonzero), FP32 k = 8 20.7 against 15.8 us, FP64 k = 16 45.4 against 37.2; of 20
+// (1.66), FP32 k = 8 50.7 against 46.4; 200,000 Zipf rows (8 steps), FP64 k = 32
+// 206 against 130; but rows of 24, sorted (1.2), FP32 k = 32 92 against 101, and
+// 30,000 rows of 4 (470 wavefronts), FP32 k = 16 6.6 against 8.9, 100,000 8.5
+// against 9.6.
+static bool spmm_masked(const SpmmFill &F, int steps, bool long_rows) {
+    return F.rows >= kSpmmBusyWaves * 64 / (long_rows ? 2 : 1) &&
+           (steps > 1 ? 2 * (F.slots + F.rows * steps / 2) >= 3 * F.nnz : F.slots + F.rows / 2 >= 2 * F.nnz);
+}
+
 template <int VD, class A, int VW, int KL>
-static hipError_t launch_spmm_t(const SpmvParams &P, int k, int nwg, hipStream_t st) {
+static hipError_t launch_spmm_t(const SpmvParams &P, const SpmmFill &F, int k, int nwg, hipStream_t st) {
     const dim3 g(nwg), b(kBlockThreads);
-    if (P.n_block_items + P.n_wave_long > 0)
-        hipLaunchKernelGGL((spmm_k<VD, A, VW, KL, true, false>), g, b, 0, st, P, k);
-    else if (P.compact == kCompactPattern)
-        hipLaunchKernelGGL((spmm_k<VD, A, VW, KL, false, true>), g, b, 0, st, P, k);
-    else
-        hipLaunchKernelGGL((spmm_k<VD, A, VW, KL, false, false>), g, b, 0, st, P, k);
+    const bool long_rows = P.n_block_items + P.n_wave_long > 0;
+    const bool mask = spmm_masked(F, spmm_steps<A, VW, KL>(), long_rows);
+    if (long_rows) {
+        if (mask) hipLaunchKernelGGL((spmm_k<VD, A, VW, KL, true, false, true>), g, b, 0, st, P, k);
+        else hipLaunchKernelGGL((spmm_k<VD, A, VW, KL, true, false, false>), g, b, 0, st, P, k);
+    } else if (P.compact == kCompactPattern) {
+        hipLaunchKernelGGL((spmm_k<VD, A, VW, KL, false, true, false>), g, b, 0, st, P, k);
+    } else {
+        if (mask) hipLaunchKernelGGL((spmm_k<VD, A, VW, KL, false, false, true>), g, b, 0, st, P, k);
+        else hipLaunchKernelGGL((spmm_k<VD, A, VW, KL, false, false, false>), g, b, 0, st, P, k);
+    }
     return hipGetLastError();
 }
 
 // lanes per row: the power of two that covers k columns
-template <int VD, class A> static hipError_t launch_spmm_v(const SpmvParams &P, int k, int nwg, hipStream_t st) {
+template <int VD, class A> static hipError_t launch_spmm_v(const SpmvParams &P, const SpmmFill &F, int k, int nwg, hipStream_t st) {
     constexpr int VW = 16 / (int)sizeof(A);
     if constexpr (sizeof(A) == 4) {
-        if (k == 2) return launch_spmm_t<VD, A, 2, 1>(P, k, nwg, st);
-        if (k == 3) return launch_spmm_t<VD, A, 2, 2>(P, k, nwg, st);
+        if (k == 2) return launch_spmm_t<VD, A, 2, 1>(P, F, k, nwg, st);
+        if (k == 3) return launch_spmm_t<VD, A, 2, 2>(P, F, k, nwg, st);
     }
-    if (k <= VW) return launch_spmm_t<VD, A, VW, 1>(P, k, nwg, st);
-    if (k <= 2 * VW) return launch_spmm_t<VD, A, VW, 2>(P, k, nwg, st);
-    if (k <= 4 * VW) return launch_spmm_t<VD, A, VW, 4>(P, k, nwg, st);
-    if (k <= 8 * VW) return launch_spmm_t<VD, A, VW, 8>(P, k, nwg, st);
-    if constexpr (sizeof(A) == 8) return launch_spmm_t<VD, A, VW, 16>(P, k, nwg, st);
+    if (k <= VW) return launch_spmm_t<VD, A, VW, 1>(P, F, k, nwg, st);
+    if (k <= 2 * VW) return launch_spmm_t<VD, A, VW, 2>(P, F, k, nwg, st);
+    if (k <= 4 * VW) return launch_spmm_t<VD, A, VW, 4>(P, F, k, nwg, st);
+    if (k <= 8 * VW) return launch_spmm_t<VD, A, VW, 8>(P, F, k, nwg, st);
+    if constexpr (sizeof(A) == 8) return launch_spmm_t<VD, A, VW, 16>(P, F, k, nwg, st);
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_spmm(const SpmvParams &P, int vdt, int vec_f64, int k, int nwg, hipStream_t st) {
+hipError_t launch_spmm(const SpmvParams &P, const SpmmFill &F, int vdt, int vec_f64, int k, int nwg, hipStream_t st) {
     if (k < 2 || k > kSpmmMax) return hipErrorInvalidValue;
     if (vec_f64) {
-        if (vdt == RGCSR_F64) return launch_spmm_v<RGCSR_F64, double>(P, k, nwg, st);
-        if (vdt == RGCSR_F32) return launch_spmm_v<RGCSR_F32, double>(P, k, nwg, st);
+        if (vdt == RGCSR_F64) return launch_spmm_v<RGCSR_F64, double>(P, F, k, nwg, st);
+        if (vdt == RGCSR_F32) return launch_spmm_v<RGCSR_F32, double>(P, F, k, nwg, st);
         return hipErrorInvalidValue;
     }
-    if (vdt == RGCSR_F32) return launch_spmm_v<RGCSR_F32, float>(P, k, nwg, st);
+    if (vdt == RGCSR_F32) return launch_spmm_v<RGCSR_F32, float>(P, F, k, nwg, st);
     return hipErrorInvalidValue;
 }
 
