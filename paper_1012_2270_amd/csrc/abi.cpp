@@ -950,15 +950,21 @@ bool panel_launch_ok(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx,
 // On the layout one lane per row stays for rows of X of at most 16 bytes,
 // which it reads in one load, unless row patterns give the columns (Zipf 10^6,
 // k = 2 and 4: 80.6 and 106.8 us against 111 and 124 with lanes sharing rows;
-// 27-point 80^3 with patterns: 25.4 and 28.1 against 19.5 and 21.9).
+// 27-point 80^3 with patterns: 25.4 and 28.1 against 19.5 and 21.9).  The
+// pattern table is one more step before the first gather, which short rows on
+// few row groups do not make up for (5-point 200^2, k = 4: 3.9 and 4.5 us;
+// 400^2: 7.0 and 4.8).
 // Four FP64 columns stay with it as well where no row is long and there are few
 // row groups or much padding (rows of 4 nonzeros in a band as they come, one
 // lane a row against lanes sharing rows: 30,000 rows 4.7 and 5.9 us, 200,000 12.7
-// and 13.2; rows of 20: 30,000 10.4 and 10.7, but 300,000 49.8 and 47.1).
+// and 13.2; rows of 20: 30,000 10.4 and 10.7, but 300,000 49.8 and 47.1; 27-point
+// 50^3 11.8 and 13.0, 80^3 48.0 and 44.9).
 bool narrow_launch_ok(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx, const void *Y, int64_t ldy, int f64) {
-    if (!lane_kernel_ok(K, X, ldx, Y, ldy, f64) || h->compact == kCompactPattern) return false;
-    return K * (f64 ? 8 : 4) <= kRunsRowBytes ||
-           (f64 && K == 4 && h->nl == 0 && (h->ns < kSpmmBusyWaves * 64 || 4 * h->slots >= 7 * h->nnz));
+    if (!lane_kernel_ok(K, X, ldx, Y, ldy, f64)) return false;
+    const bool few = h->ns < kSpmmBusyWaves * 64;
+    if (K * (f64 ? 8 : 4) <= kRunsRowBytes)
+        return h->compact != kCompactPattern || (h->ns < kSpmmBusyWaves * 32 && h->compact_width <= 8);
+    return f64 && K == 4 && h->nl == 0 && (few || (h->compact != kCompactPattern && 4 * h->slots >= 7 * h->nnz));
 }
 
 void spmv_launch(const rgcsr_matrix_s *h, int K, const void *X, int64_t ldx, void *Y, int64_t ldy, int f64,
