@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kBlockThreads) void spmv_pattern_k(SpmvParams P) {
 
 // Row patterns whose x comes from LDS (PatSegs): 27 steps issue 27 value loads
 // and 10 of x instead of 27 gathers, all before anything waits (27-point 101^3,
-// FP64: 48.0 -> 40.7 us, 5.8 TB/s).  Where they pay: runs_pay below.  NS: the runs, a constant, as a count read from
+// FP64: 48.0 -> 40.7 us, 5.8 TB/s).  Where they pay: runs_width below.  NS: the runs, a constant, as a count read from
 // memory made each run's load wait for a scalar load of its own (FP32 96^3:
 // 24.8 us); further ones repeat the last.
 template <int VD, class A, int U, int NS, bool DOT>
@@ -358,29 +358,29 @@ static hipError_t launch_segment_v(const SpmvParams &P, int32_t width, int nwg, 
     return hipGetLastError();
 }
 
-// x from LDS runs pays for 8-byte vectors of rows wide enough against the loads
-// of the kernel that is compiled (3 or 9 runs, and their ends).  400,000 rows
-// on diagonals in k runs of w, one handle repeated, gathered against runs.  FP64:
-//   1 x 6   6.0, 6.6 us    3 x 3   7.4,  6.9    1 x 17  13.7, 11.2    3 x 9  19.9, 15.6
+// x from LDS runs pays for rows wide enough against the loads of the kernel
+// that is compiled (3 or 9 runs, and their ends).  400,000 rows on diagonals in
+// k runs of w, one handle repeated, gathered against runs, us.  FP64:
+//   1 x 6   6.0, 6.6       3 x 3   7.4, 6.9     1 x 17  13.7, 11.2    3 x 9  19.9, 15.6
 //   4 x 4  12.1, 12.8      5 x 3  12.2, 12.2    6 x 3   13.7, 13.1    9 x 3  20.1, 17.2
 // FP32 values with FP64 vectors:
 //   3 x 5   7.9, 8.5       1 x 17  9.3, 8.7     3 x 9   13.1, 10.6    9 x 3  13.1, 13.2
-// FP32 vectors gather, with 16-bit values too: what the runs save on requests
-// the longer way to the first step costs (9 x 3 9.0, 11.5; 3 x 9 8.7, 8.9; 4 x 3
-// 5.0, 9.1; 27-point 96^3 in BF16 16.1, 18.6).
-static bool runs_pay(int vd, int32_t runs, int32_t width) {
-    if (vd == RGCSR_F64) return width >= (runs <= 3 ? 8 : 18);
-    return runs <= 3 && width >= 16;
+// FP32: 3 x 3 4.8, 5.8; 4 x 3 5.0, 9.1; 5 x 5 8.8, 11.2; 1 x 17 6.6, 7.7; but 27 points
+// on a grid of 30 x 200 x 200 (3 runs) 28.4, 22.5, and of 160^3 (9 runs) 84.0, 83.3, with
+// p.q 1.5% of a solve.  16-bit values gather: what the runs save on requests the
+// longer way to the first step costs (27-point 96^3 in BF16 16.1, 18.6).
+template <int VD, class A> constexpr int32_t runs_width(bool three) {
+    if (VD == RGCSR_F64) return three ? 8 : 18;
+    return three ? (sizeof(A) == 8 ? 16 : 18) : 27;
 }
 
 template <int VD, class A, bool DOT>
 static hipError_t launch_pattern_v(const SpmvParams &P, int32_t rows, int32_t width, int nwg, const PatSegs *segs,
                                    hipStream_t st) {
-    if constexpr (sizeof(A) == 8)
-        if (segs && runs_pay(VD, segs->n, width)) {
+    if constexpr (VD == RGCSR_F64 || VD == RGCSR_F32)
+        if (segs && width >= runs_width<VD, A>(segs->n <= 3)) {
             if (segs->n <= 3) return launch_segment_v<VD, A, 3, DOT>(P, width, nwg, *segs, st);
-            if constexpr (VD == RGCSR_F64)
-                return launch_segment_v<VD, A, kPatSegs, DOT>(P, width, nwg, *segs, st);
+            return launch_segment_v<VD, A, kPatSegs, DOT>(P, width, nwg, *segs, st);
         }
     if (rows == 2) {
         switch (pattern_steps(width, {4, 5, 7, 8})) {
@@ -436,6 +436,7 @@ hipError_t launch_spmv_compact(const SpmvParams &P, int vdt, int vec_f64, int32_
 // ---------------------------------------------------------------------------
 // Pattern search on device CSR arrays
 // ---------------------------------------------------------------------------
+// (the same combination as on the host)
 __device__ __forceinline__ uint64_t pat_mix(uint64_t h, uint64_t v) {
     h ^= v + 0x9e3779b97f4a7c15ull + (h << 6) + (h >> 2);
     h *= 0xff51afd7ed558ccdull;

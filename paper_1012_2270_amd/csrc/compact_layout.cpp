@@ -10,6 +10,8 @@ namespace rg {
 
 namespace {
 
+// (constants: the golden ratio, and the first multiplier of the published
+// MurmurHash3 64-bit finalizer)
 uint64_t mix(uint64_t h, uint64_t v) {
     h ^= v + 0x9e3779b97f4a7c15ull + (h << 6) + (h >> 2);
     h *= 0xff51afd7ed558ccdull;

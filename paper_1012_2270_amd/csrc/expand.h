@@ -13,7 +13,9 @@
 //            LDS, and multiplies the layout's values against them.
 // The entries of a (tile, unit) pair are contiguous in both orders, padded to
 // whole runs.  Only the pattern is stored a second time: values are the
-// layout's, so a value update has nothing to follow.
+// layout's, so a value update has nothing to follow.  The runs of x entries are
+// one buffer of the handle, which every product writes, as the tiles' partial
+// sums are: products of one handle have to be ordered with each other.
 #pragma once
 
 #include <hip/hip_runtime_api.h>

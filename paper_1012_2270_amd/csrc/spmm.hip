@@ -11,9 +11,9 @@
 //
 // Bound by the X requests.  With blocks of 16, 8, 4, 2 and 1 columns and one
 // lane per row before: 27-point 80^3 FP32, k = 7 (rows of 28 bytes, four
-// launches) 134.7 -> 31.6 us, k = 16 93.4 -> 63.4, k = 32 223 -> 111; Zipf
-// 10^6, k = 7 499 -> 152, k = 31 2379 -> 298, k = 32 191 -> 175; FP64 27-point
-// 60^3, k = 17 777 -> 95.
+// launches) 134.3 -> 32.0 us, k = 16 91.6 -> 61.6, k = 32 224 -> 115; Zipf
+// 10^6, k = 7 501 -> 148, k = 31 2383 -> 275, k = 32 198 -> 173; FP64 27-point
+// 60^3, k = 17 775 -> 89.
 #include <hip/hip_runtime.h>
 
 #include "compact.h"
