@@ -23,27 +23,37 @@ uint64_t mix(uint64_t h, uint64_t v) {
 bool find_patterns(const HostLayout &L, HostCompact &C) {
     std::vector<std::vector<int32_t>> lists;
     std::unordered_map<uint64_t, int32_t> seen;
-    std::vector<int32_t> cur;
+    std::vector<int32_t> cur, step, differs;
     int32_t longest = 0, last = -1;
     C.pat_id.resize((size_t)L.ns);
     for (int64_t g = 0; g < L.ng; g++) {
         const int64_t r0 = L.ragged ? L.grp_row0[g] : g * L.G;
         const int64_t r1 = L.ragged ? L.grp_row0[g + 1] : std::min<int64_t>(L.ns, r0 + L.G);
         const int64_t sg = r1 - r0;
+        const int64_t width = sg ? (L.group_end(g) - L.gp[g]) / sg : 0;
+        if (width > kPatLen) return false;
+        // Neighbouring rows mostly share a list: a row of the length before it
+        // whose columns are all as far from that row's as the rows are apart
+        // (padding repeats the last column), told step by step, rows side by
+        // side as they lie (1.8M nonzeros: row by row 3.4 ms).
+        step.assign((size_t)sg, 0);
+        differs.assign((size_t)sg, 1);
+        for (int64_t i = 1; i < sg; i++) {
+            step[i] = L.short_row[r0 + i] - L.short_row[r0 + i - 1];
+            differs[i] = L.short_len[r0 + i] != L.short_len[r0 + i - 1];
+        }
+        for (int64_t j = 0; j < width; j++) {
+            const int32_t *c = &L.slot_col[L.gp[g] + j * sg], *st = step.data();
+            int32_t *df = differs.data();
+            for (int64_t i = 1; i < sg; i++) df[i] |= (uint32_t)c[i] - (uint32_t)c[i - 1] != (uint32_t)st[i];
+        }
         for (int64_t i = r0; i < r1; i++) {
-            const int32_t len = L.short_len[i];
-            if (len > kPatLen) return false;
-            const int64_t row = L.short_row[i], s0 = L.gp[g] + (i - r0);
-            // neighbouring rows mostly share a list
-            if (last >= 0 && (int32_t)lists[last].size() == len) {
-                const std::vector<int32_t> &p = lists[last];
-                int32_t j = 0;
-                while (j < len && (int64_t)L.slot_col[s0 + j * sg] - row == p[j]) j++;
-                if (j == len) {
-                    C.pat_id[i] = (uint8_t)last;
-                    continue;
-                }
+            if (!differs[i - r0]) {
+                C.pat_id[i] = (uint8_t)last;
+                continue;
             }
+            const int32_t len = L.short_len[i];
+            const int64_t row = L.short_row[i], s0 = L.gp[g] + (i - r0);
             cur.resize(len);
             uint64_t h = mix(0, (uint64_t)len);
             for (int32_t j = 0; j < len; j++) {
@@ -124,12 +134,14 @@ bool find_windows(const HostLayout &L, HostCompact &C) {
         for (int64_t g = u * per; g < std::min(L.ng, (u + 1) * per); g++) {
             const int64_t r0 = L.ragged ? L.grp_row0[g] : g * L.G;
             const int64_t r1 = L.ragged ? L.grp_row0[g + 1] : std::min<int64_t>(L.ns, r0 + L.G);
-            for (int64_t i = r0; i < r1; i++) {
-                const int32_t len = L.short_len[i];
-                if (!len) continue;
-                const int64_t s0 = L.gp[g] + (i - r0);
-                lo = std::min<int64_t>(lo, L.slot_col[s0]);
-                hi = std::max<int64_t>(hi, L.slot_col[s0 + (len - 1) * (r1 - r0)]);
+            const int64_t width = r1 > r0 ? (L.group_end(g) - L.gp[g]) / (r1 - r0) : 0;
+            if (width == 0) continue;
+            // a row's first column lies in the first step and its last one in
+            // the last (padding repeats it; 0 for an empty row)
+            const int32_t *first = &L.slot_col[L.gp[g]], *final = first + (width - 1) * (r1 - r0);
+            for (int64_t i = 0; i < r1 - r0; i++) {
+                if (L.short_len[r0 + i]) lo = std::min<int64_t>(lo, first[i]);
+                hi = std::max<int64_t>(hi, final[i]);
             }
         }
         if (hi < 0) continue;  // a unit of empty rows
@@ -142,8 +154,10 @@ bool find_windows(const HostLayout &L, HostCompact &C) {
     C.col16.assign((size_t)L.slots, 0);
     for (int64_t g = 0; g < L.ng; g++) {
         const int32_t base = C.win[2 * (g / per)];
-        for (int64_t s = L.gp[g]; s < L.group_end(g); s++)
-            C.col16[s] = (uint16_t)std::max(L.slot_col[s] - base, 0);
+        const int64_t end = L.group_end(g);
+        const int32_t *c = L.slot_col.data();
+        uint16_t *o = C.col16.data();
+        for (int64_t s = L.gp[g]; s < end; s++) o[s] = (uint16_t)std::max(c[s] - base, 0);
     }
     return true;
 }
