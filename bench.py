@@ -49,7 +49,8 @@ def alg_bytes(nnz, n_rows, n_cols, groups, s_v=4, s_x=4, s_y=4, k=1):
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("kernels.hip", "kernels.h", "internal.h", "tiles.hip", "tiles.h"):
+    for f in ("kernels.hip", "kernels.h", "internal.h", "device.h", "compact.hip", "compact.h", "expand.hip", "expand.h",
+              "spmm.hip", "spmm.h", "tiles.hip", "tiles.h"):
         with open(os.path.join(ROOT, "paper_1012_2270_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
