@@ -126,7 +126,24 @@ typedef struct {
                                stay on the long-row path.  0 = off; -1 (default) = 256, used only when the
                                tiled rows hold at least 262,144 nonzeros.  F32 storage
                                with F64 vectors runs the tiled rows on the long-row
-                               path. */
+                               path.
+                               With -1 a handle that owns its memory (not one of a
+                               plan), with group_size 64, lanes_per_row 1 and the
+                               automatic schedule (rows_per_lane 0, pad_loads -1,
+                               load_policy 0) takes the two-step SpMV in the tiles'
+                               place where it pays: for the same vectors, one launch
+                               writes x at the columns of the entries, tile by tile
+                               from LDS, to a buffer of the handle, and a second one
+                               multiplies every row from it.  It needs at least 12
+                               nonzeros on average for each pair of a column tile
+                               (16,384 columns; 8,192 for F64 storage) and a unit of
+                               about 4,096 entries, at most 1,024 such tiles, and
+                               2,200,000 nonzeros in F64 storage.  It stores no tiles but 4 bytes and a vector
+                               element per nonzero, and those of padding to whole runs
+                               of 16 (8 to 10 bytes a nonzero with F32 vectors, 12 to
+                               16 with F64), in device memory of its own.  Its sums run
+                               in another order than the tiles': a handle built from a
+                               plan may differ from it in the last bits. */
     int32_t col_panels;     /* 0 (default) = off.  P = 8, 16, ..., 64: the handle also
                                keeps a copy of the matrix for launches of several
                                right-hand sides.  The columns are split into P panels
@@ -178,7 +195,10 @@ typedef struct {
     int64_t sort_window, long_row_threshold;
     int64_t device_bytes; /* device memory the handle owns */
     int32_t rows_per_lane, pad_loads, load_policy; /* kernel schedule in use */
-    int64_t tiled_rows, tile_entries, n_tiles;     /* column-tiled long rows (tile_min_len) */
+    int64_t tiled_rows, tile_entries, n_tiles;     /* long rows selected for column tiles
+                                                      (tile_min_len), also where the
+                                                      two-step SpMV stands in their place
+                                                      and no tile is stored */
     int64_t col_panels, panel_pieces;              /* column panels and their pieces (col_panels) */
 } rgcsr_info_t;
 
@@ -210,7 +230,8 @@ rgcsr_status rgcsr_layout_host(int64_t n_rows, int64_t n_cols, int64_t nnz,
 
 /* Sizes of the column-tiled copy (rgcsr_opts.tile_min_len) of a host CSR
  * matrix under *opts, without a GPU: the rows that a handle built with the
- * same options stores split by column tile as well.  *n_tiles receives the
+ * same options from a plan stores split by column tile as well (one that owns
+ * its memory may take the two-step SpMV instead, see tile_min_len).  *n_tiles receives the
  * tiles (n_cols / 8,192 rounded up, or / 4,096 for F64 value_dtype; 0 when no
  * row is tiled), *tiled_rows and *tile_entries the rows and nonzeros tiled,
  * *units the workgroups of the tile kernel (empty ones that even out the XCD
@@ -251,7 +272,14 @@ rgcsr_status rgcsr_panel_sizes(int64_t n_rows, int64_t n_cols, int64_t nnz,
  * host and converted there.  The device path allocates temporary device
  * memory (freed before return).  The handle owns the device arrays it
  * allocates (hipMalloc); the call synchronises the stream before returning,
- * so the handle is ready. */
+ * so the handle is ready.
+ *
+ * Beside the layout a handle may keep a shorter form of its column indices
+ * for products with one vector, with the same results: a byte per row and a
+ * table of at most 8 KB (rows on few lists of offsets from the diagonal), or
+ * 2 bytes per slot (columns in a band), under the automatic schedule with
+ * lanes_per_row 1, group_size a multiple of 64 and no long rows.
+ * rgcsr_info's device_bytes counts them. */
 rgcsr_status rgcsr_from_csr(int64_t n_rows, int64_t n_cols, int64_t nnz,
                             const int64_t *row_ptr, const int32_t *col_idx,
                             const void *vals, rgcsr_dtype vals_dtype,
@@ -313,8 +341,18 @@ rgcsr_status rgcsr_batch_offsets(rgcsr_handle A, int64_t *row_off, int64_t *col_
 /* rgcsr_spmv: y = A x (Section 3.4 kernel semantics: every row is
  * overwritten, empty rows give 0).  x[n_cols], y[n_rows] are device pointers
  * of vec_dtype (F32 or F64); x and y must not overlap.  One kernel launch,
- * plus a second small one that adds chunk partial sums in a fixed order when
- * some row has more than 16,384 nonzeros (deterministic results). */
+ * or two with column tiles or the two-step SpMV (tile_min_len), plus a small
+ * one that adds chunk partial sums in a fixed order when some row has more
+ * than 16,384 nonzeros (deterministic results).
+ *
+ * Calls on one handle that writes to a buffer of its own must be ordered with
+ * each other, by one stream or by events, a replayed graph included: products
+ * that overlap read each other's partial results.  Those are handles with
+ * column tiles or the two-step SpMV (rgcsr_info: tiled_rows > 0), with rows of
+ * more than 16,384 nonzeros (partials > 0), and with col_panels for several
+ * right-hand sides; the same holds for the transpose that
+ * rgcsr_spmv_transpose_grad multiplies by.  rgcsr_clone gives a handle with
+ * buffers of its own.  Products of other handles may overlap. */
 rgcsr_status rgcsr_spmv(rgcsr_handle A, const void *x, void *y, rgcsr_dtype vec_dtype,
                         void *stream);
 
@@ -485,7 +523,8 @@ typedef struct {
  * square shape; pass the same handle for a pure single-matrix refinement
  * when A_lo stores F32.  b and x are device float64 arrays of n; x holds the
  * initial guess and receives the solution.  Allocates its own device
- * workspace (freed before return) and synchronises the stream. */
+ * workspace and a few bytes of pinned host memory, which the convergence test
+ * is read from (freed before return), and synchronises the stream. */
 rgcsr_status rgcsr_cg_solve(rgcsr_handle A_lo, rgcsr_handle A_hi, const double *b, double *x,
                             double tol, double inner_tol, int32_t max_outer, int32_t max_inner,
                             void *stream, rgcsr_cg_stats *stats);
