@@ -245,17 +245,20 @@ __global__ __launch_bounds__(kBlockThreads) void spmm_k(SpmvParams P, int32_t k)
 // (1.66), FP32 k = 8 50.7 against 46.4; 200,000 Zipf rows (8 steps), FP64 k = 32
 // 206 against 130; but rows of 24, sorted (1.2), FP32 k = 32 92 against 101, and
 // 30,000 rows of 4 (470 wavefronts), FP32 k = 16 6.6 against 8.9, 100,000 8.5
-// against 9.6.
-static bool spmm_masked(const SpmmFill &F, int steps, bool long_rows) {
-    return F.rows >= kSpmmBusyWaves * 64 / (long_rows ? 2 : 1) &&
-           (steps > 1 ? 2 * (F.slots + F.rows * steps / 2) >= 3 * F.nnz : F.slots + F.rows / 2 >= 2 * F.nnz);
+// against 9.6.  Beside long rows one step in flight needs 3/2 as well (Zipf 10^6,
+// tau = 6, 1.7 steps: FP64 k = 32 390 against 331), and in FP64 no number of rows
+// (30,000 Zipf rows: 77 against 58).
+static bool spmm_masked(const SpmmFill &F, int steps, bool long_rows, bool f64) {
+    const bool busy = F.rows >= kSpmmBusyWaves * 64 / (long_rows ? 2 : 1) || (long_rows && f64 && steps == 1);
+    const int64_t walked = F.slots + F.rows * steps / 2;
+    return busy && (steps > 1 || long_rows ? 2 * walked >= 3 * F.nnz : walked >= 2 * F.nnz);
 }
 
 template <int VD, class A, int VW, int KL>
 static hipError_t launch_spmm_t(const SpmvParams &P, const SpmmFill &F, int k, int nwg, hipStream_t st) {
     const dim3 g(nwg), b(kBlockThreads);
     const bool long_rows = P.n_block_items + P.n_wave_long > 0;
-    const bool mask = spmm_masked(F, spmm_steps<A, VW, KL>(), long_rows);
+    const bool mask = spmm_masked(F, spmm_steps<A, VW, KL>(), long_rows, sizeof(A) == 8);
     if (long_rows) {
         if (mask) hipLaunchKernelGGL((spmm_k<VD, A, VW, KL, true, false, true>), g, b, 0, st, P, k);
         else hipLaunchKernelGGL((spmm_k<VD, A, VW, KL, true, false, false>), g, b, 0, st, P, k);
